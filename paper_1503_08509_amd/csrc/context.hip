@@ -208,12 +208,11 @@ struct fep3m_ctx {
   std::vector<MGLevel> lv;
   std::vector<Transfer> tr;
   std::vector<TransferF> trf;
-  // fine-level residual restricted inside the operator (p 5 -> 3, n even):
-  // per-tile partial coarse values, float64 or float32 like the V-cycle
+  // fine-level residual restricted inside the operator (order 4..6 to 3):
+  // per-block partial coarse values, float64 or float32 like the V-cycle
   bool fuse_rr = false;
   double *rrp_d = nullptr;
   float *rrp_f = nullptr;
-  template <class T> T *rr_part() const;
   bool mixed = false;        // float32 V-cycle, float32 near field and interpolation
   template <class T> const TransferT<T> &transfer(int l) const;
   double *dot_scr = nullptr; // two-dot partials of the mixed PCG
@@ -339,14 +338,25 @@ struct fep3m_ctx {
     hip_check(hipEventRecord(prof.stage_ev[2 * slot + (begin ? 0 : 1)], stream), "event");
     if (begin) prof.marked |= 1u << slot;
   }
+  int launch_restrict0(const double *x, const double *f, double *fc) {
+    return launch_march_restrict(stream, nb, nbs, lv[0].op, tr[0], x, f, rrp_d, fc);
+  }
+  int launch_restrict0(const float *x, const float *f, float *fc) {
+    return launch_apply_restrict_f32(stream, nbs, lv[0].opf, trf[0], x, f, rrp_f, fc);
+  }
+  int launch_dot0(const double *x, double *out, double *part) {
+    return launch_apply_tiles(stream, nbs, lv[0].op, x, out, part);
+  }
+  int launch_dot0(const float *, float *, double *) { return -1; }
   // fine-level operator launch, bracketed by events when profiling
   template <class T>
   int apply0(const T *x, const T *f, T *out, const T *d, T *xo, T c1, T c2, int mode, double *part, T s0 = T(0)) {
     const bool rec = prof.on && prof.kused < int(prof.kev.size()) / 2;
     if (rec) hip_check(hipEventRecord(prof.kev[2 * prof.kused], stream), "event");
-    const int K = mode == kResidualRestrict
-                      ? launch_apply_restrict<T>(stream, nbs, lv[0].oper<T>(), transfer<T>(0), x, f, rr_part<T>())
-                      : launch_apply<T>(stream, nbs, lv[0].oper<T>(), x, f, out, d, xo, c1, c2, mode, part, s0);
+    const int K = mode == kResidualRestrict   // out: the next level's right side
+                      ? launch_restrict0(x, f, out)
+                  : mode == kApplyDot && mixed ? launch_dot0(x, out, part)
+                      : launch_apply<T>(stream, nb, nbs, lv[0].oper<T>(), x, f, out, d, xo, c1, c2, mode, part, s0);
     if (K < 0) throw Status(FEP3M_ERR_UNSUPPORTED, "fine-level operator variant");
     if (rec) {
       hip_check(hipEventRecord(prof.kev[2 * prof.kused + 1], stream), "event");
@@ -555,7 +565,7 @@ void fep3m_ctx::build(double L_, const std::vector<int64_t> &Ns, int n_, int q_,
   else if (opt.solver == FEP3M_SOLVER_FDM) build_fdm();
   // partials serve every two-stage reduction: the fixed reduction grids and
   // the per-tile partials of the fine-level operator
-  partial_len = std::max(partial_len, size_t(2) * nb * apply_blocks(lv[0].op) + 64);
+  partial_len = std::max(partial_len, size_t(2) * nb * std::max(march_blocks(p, n, nb), mixed ? apply_tiles(n) : 0) + 64);
   // row-wise mesh kernels: nb K <= max(kRowBlocks, nb) partials (nb <= 2048 systems)
   partial_len = std::max(partial_len, size_t(kRowBlocks) + 64);
   partial = alloc<double>(partial_len, "partials");
@@ -616,8 +626,6 @@ static Transfer make_transfer(int pf, int nf, int pc, int nc) {
 
 template <> const Transfer &fep3m_ctx::transfer<double>(int l) const { return tr[l]; }
 template <> const TransferF &fep3m_ctx::transfer<float>(int l) const { return trf[l]; }
-template <> double *fep3m_ctx::rr_part<double>() const { return rrp_d; }
-template <> float *fep3m_ctx::rr_part<float>() const { return rrp_f; }
 
 void fep3m_ctx::build_mg() {
   std::vector<std::pair<int, int>> hier;
@@ -637,6 +645,7 @@ void fep3m_ctx::build_mg() {
   }
   for (size_t i = 0; i + 1 < hier.size(); ++i)
     tr.push_back(make_transfer(hier[i].first, hier[i].second, hier[i + 1].first, hier[i + 1].second));
+  fuse_rr = p > 3 && (!mixed || n % 2 == 0);   // order p to order 3 on the same elements
   for (size_t i = 0; i < lv.size(); ++i) {
     MGLevel &L_ = lv[i];
     const size_t nv = L_.ndof * 2 * nb;   // one block of the level per system (forward and adjoint)
@@ -646,7 +655,7 @@ void fep3m_ctx::build_mg() {
       L_.vd.f = (i == 0) ? nullptr : alloc<double>(nv, "mg f");
       if (i + 1 < lv.size()) {
         L_.vd.x2 = alloc<double>(nv, "mg x2");
-        L_.vd.r = alloc<double>(nv, "mg r");
+        if (i > 0 || !fuse_rr) L_.vd.r = alloc<double>(nv, "mg r");
       }
     } else {
       // float32 hierarchy; the fine level also holds the float32 copy of the residual
@@ -655,33 +664,13 @@ void fep3m_ctx::build_mg() {
       L_.vf.f = alloc<float>(nv, "mg f (f32)");
       if (i + 1 < lv.size()) {
         L_.vf.x2 = alloc<float>(nv, "mg x2 (f32)");
-        L_.vf.r = alloc<float>(nv, "mg r (f32)");
-      }
-    }
-    if (L_.op.p == 6) {   // the order-6 operator reads its band coefficients from device memory
-      constexpr int Q2 = 49;
-      std::vector<double> cd(2 * Q2);
-      for (int k = 0; k < Q2; ++k) {
-        cd[k] = L_.op.me[k];
-        cd[Q2 + k] = L_.op.ke[k];
-      }
-      double *g = alloc<double>(cd.size(), "order-6 operator coefficients");
-      hip_check(hipMemcpy(g, cd.data(), cd.size() * sizeof(double), hipMemcpyHostToDevice), "upload coefficients");
-      L_.op.cg = g;
-      if (mixed) {
-        std::vector<float> cf(cd.size());
-        for (size_t k = 0; k < cf.size(); ++k) cf[k] = k < Q2 ? L_.opf.me[k] : L_.opf.ke[k - Q2];
-        float *gf = alloc<float>(cf.size(), "order-6 operator coefficients (f32)");
-        hip_check(hipMemcpy(gf, cf.data(), cf.size() * sizeof(float), hipMemcpyHostToDevice), "upload coefficients");
-        L_.opf.cg = gf;
+        if (i > 0 || !fuse_rr) L_.vf.r = alloc<float>(nv, "mg r (f32)");
       }
     }
   }
-  fuse_rr = lv.size() > 1 && lv[0].op.p == 5 && lv[1].op.p == 3 && n % 2 == 0;
   if (fuse_rr) {
-    const size_t np = size_t(2) * nb * (n / 2) * (n / 2) * (n / 2) * 343;   // per system and tile
-    if (mixed) rrp_f = alloc<float>(np, "restriction partials (f32)");
-    else rrp_d = alloc<double>(np, "restriction partials");
+    if (mixed) rrp_f = alloc<float>(size_t(2) * nb * (n / 2) * (n / 2) * (n / 2) * 343, "restriction partials (f32)");
+    else rrp_d = alloc<double>(size_t(2) * nb * march_restrict_size(p, n, nb), "restriction partials");
   }
   if (mixed) {
     for (const Transfer &t : tr) trf.push_back(t.cast<float>());
@@ -839,7 +828,7 @@ void fep3m_ctx::estimate_spectra() {
     // every configuration has the same operator: iterate on configuration 0
     double nx = std::sqrt(reduce_host(launch_dot(stream, 1, L_.ndof, xw, xw, partial), partial, 0));
     for (int it = 0; it < 24; ++it) {
-      launch_apply<double>(stream, 1, L_.op, xw, nullptr, L_.d, nullptr, nullptr, 0.0, 0.0, kDinvApply, nullptr);
+      launch_apply<double>(stream, nb, 1, L_.op, xw, nullptr, L_.d, nullptr, nullptr, 0.0, 0.0, kDinvApply, nullptr);
       double nd = std::sqrt(reduce_host(launch_dot(stream, 1, L_.ndof, L_.d, L_.d, partial), partial, 0));
       lam = nd / nx;
       launch_scale(stream, L_.ndof, 1.0 / nd, L_.d, xw);
@@ -893,7 +882,7 @@ int fep3m_ctx::cheb_smooth(int l, const T *f, bool zero_start, double *dot_part)
       const T *xprev = (mode == kCheb || mode == kChebDot) ? V.x2 : nullptr;
       double *part = dot ? dot_part : nullptr;
       const int K = l == 0 ? apply0<T>(xin, f, nullptr, xprev, V.x2, T(c1), T(c2), mode, part, T(s0))
-                           : launch_apply<T>(stream, nbs, op, xin, f, nullptr, xprev, V.x2, T(c1), T(c2), mode, part,
+                           : launch_apply<T>(stream, nb, nbs, op, xin, f, nullptr, xprev, V.x2, T(c1), T(c2), mode, part,
                                              T(s0));
       if (dot) Kd = K;
       std::swap(V.x, V.x2);
@@ -917,11 +906,10 @@ int fep3m_ctx::vcycle(int l, const T *f, double *dot_part) {
   LevelVecs<T> &Vc = lv[l + 1].vec<T>();
   cheb_smooth<T>(l, f, true);
   if (l == 0 && fuse_rr) {   // residual restricted in the operator's epilogue, never stored
-    apply0<T>(V.x, f, nullptr, nullptr, nullptr, T(0), T(0), kResidualRestrict, nullptr);
-    launch_restrict_sum<T>(stream, nbs, n, rr_part<T>(), Vc.f);
+    apply0<T>(V.x, f, Vc.f, nullptr, nullptr, T(0), T(0), kResidualRestrict, nullptr);
   } else {
     if (l == 0) apply0<T>(V.x, f, V.r, nullptr, nullptr, T(0), T(0), kResidual, nullptr);
-    else launch_apply<T>(stream, nbs, op, V.x, f, V.r, nullptr, nullptr, T(0), T(0), kResidual, nullptr);
+    else launch_apply<T>(stream, nb, nbs, op, V.x, f, V.r, nullptr, nullptr, T(0), T(0), kResidual, nullptr);
     launch_transfer<T>(stream, nbs, transfer<T>(l), V.r, Vc.f, true);
   }
   vcycle<T>(l + 1, Vc.f);

@@ -23,7 +23,6 @@ struct LevelOpT {
   T me[(kMaxP + 1) * (kMaxP + 1)];  // element mass
   T dk[kMaxP];           // diagonal of assembled K1 at local index k (k = 0: vertex)
   T dm[kMaxP];           // diagonal of assembled M1
-  const T *cg = nullptr; // device copy of me then ke (p = 6 levels: read through scalar loads)
 
   template <class U>
   LevelOpT<U> cast() const {
@@ -101,7 +100,7 @@ enum ApplyMode : int {
   // x1 = s0 D^-1 f is never stored:
   kChebZ2 = 5,     // as kCheb with x = s0 D^-1 f (built from f on the fly) and x_prev = 0
   kChebZ3 = 6,     // as kCheb with x_prev = s0 D^-1 f
-  kResidualRestrict = 7,  // f - K x restricted to the next level, not stored (launch_apply_restrict)
+  kResidualRestrict = 7,  // f - K x restricted to the next level, not stored (launch_march_restrict)
   kChebDot = 8     // as kCheb, and block partials of x_new . f
 };
 

@@ -9,38 +9,9 @@
 // mesh, Section 2.2), applied as y = Kx (My Mz x) + Mx (Ky Mz x + My Kz x)
 // with banded 1-D passes over register columns of an LDS-staged tile.
 #include "kernels.hpp"
+#include "mesh_device.hpp"
 
 namespace fep3m {
-
-// Periodic wrap of an index known to lie in [-P, 2P).
-__device__ __forceinline__ int wrapi(int i, int P) { return i < 0 ? i + P : (i >= P ? i - P : i); }
-
-__device__ __forceinline__ double block_sum(double v, double *red) {
-  // Fixed-shape tree over the block (deterministic).
-  const int t = threadIdx.x;
-  red[t] = v;
-  __syncthreads();
-  for (int s = blockDim.x >> 1; s > 0; s >>= 1) {
-    if (t < s) red[t] += red[t + s];
-    __syncthreads();
-  }
-  double r = red[0];
-  __syncthreads();
-  return r;
-}
-
-// Fixed-shape block sum for any block of whole waves (up to 8): shuffle
-// tree inside each wave, then the wave sums in order.  The result is valid
-// in thread 0.
-__device__ __forceinline__ double block_sum_waves(double v, double *red) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double r = 0.0;
-  if (threadIdx.x == 0)
-    for (int w = 0; w < int(blockDim.x >> 6); ++w) r += red[w];
-  return r;
-}
 
 // ----------------------------------------------------------------- load
 
@@ -186,17 +157,6 @@ __device__ __forceinline__ void tile_coords(int b, int tiles, int &tx, int &ty, 
   }
 }
 
-// An entry of op.dk / op.dm at a run-time local index, as a select over the
-// compile-time indices: an indexed read of the by-value operator argument
-// would copy the whole operator to scratch memory.
-template <int PO, class T>
-__device__ __forceinline__ T pick(const T (&v)[kMaxP], int k) {
-  T r = v[0];
-#pragma unroll
-  for (int j = 1; j < PO; ++j) r = (k == j) ? v[j] : r;
-  return r;
-}
-
 template <int PO, int TE, int NT = 256>
 struct ApplyShape {
   static constexpr int O = TE * PO;          // owned nodes per axis
@@ -211,36 +171,6 @@ struct ApplyShape {
   static constexpr int LDS = LDS_AB > LDS_C + LDS_Y ? LDS_AB : LDS_C + LDS_Y;
   static_assert(I * I <= NT && O * I <= NT && O * O <= NT, "tile columns must fit one pass of the block");
 };
-
-// Banded 1-D element-assembled operator on a column held in registers:
-// out[o] = sum_j a[k][j] v[o + PO - k + j] (+ a[PO][j] v[o + j] for k = 0),
-// k = o mod PO, with v indexed from one element below the first output.
-// Every coefficient index is a compile-time constant, so the (wave-uniform)
-// coefficients come from scalar registers.
-template <int PO, int NOUT, class T>
-__device__ __forceinline__ void band_apply(const T *__restrict__ a, const T (&v)[NOUT + PO + 1], T (&out)[NOUT]) {
-  constexpr int Q1 = PO + 1;
-#pragma unroll
-  for (int o = 0; o < NOUT; ++o) {
-    const int k = o % PO;
-    T s = T(0);
-#pragma unroll
-    for (int j = 0; j < Q1; ++j) s += a[k * Q1 + j] * v[o + PO - k + j];
-    if (k == 0) {
-#pragma unroll
-      for (int j = 0; j < Q1; ++j) s += a[PO * Q1 + j] * v[o + j];
-    }
-    out[o] = s;
-  }
-}
-
-template <int PO, int NOUT, class T>
-__device__ __forceinline__ void band_apply_acc(const T *__restrict__ a, const T (&v)[NOUT + PO + 1], T (&out)[NOUT]) {
-  T t[NOUT];
-  band_apply<PO, NOUT>(a, v, t);
-#pragma unroll
-  for (int o = 0; o < NOUT; ++o) out[o] += t[o];
-}
 
 // Residual restricted in the operator's epilogue (p = 5 to p = 3 on the same
 // elements, whole 2^3-element tiles): 1-D weights w[s][j] (fine node s of an
@@ -278,38 +208,32 @@ __device__ __forceinline__ void restrict_partial(const T *__restrict__ w, const 
   o[6] = s;
 }
 
-// One tile of TE^3 elements per block: y = K x on the owned nodes, then the
-// mode's epilogue.  The owned nodes of a tile are p*e + k, k < p, for its
-// elements; the inputs reach one element below and one node above.
+// The operator on one tile of TE^3 elements per block: y = K x on the owned
+// nodes, then the mode's epilogue.  Used on the order-1 levels.  Orders 3 to
+// 6 run k_march.hip, except in mixed precision at p = 5 the float64 operator
+// of the PCG and the float32 residual restricted in place (RR): k_march.hip
+// adds in another order, and there a last-bit change turns float32 roundings
+// of the element field over (up to 1.4e-7 of the potentials' RMS at single
+// charges).
+// The owned nodes of a tile are p*e + k, k < p, for its elements; the inputs
+// reach one element below and one node above.
 // Pass z: each thread streams one (x, y) column of the input from global
 // memory and writes A = Mz x, B = Kz x; pass y: one (z, x) column of A and B
 // gives C1 = My A and C2 = Ky A + My B; pass x: one (z, y) row of C1, C2
 // gives y = Kx C1 + Mx C2; the epilogue then walks the owned nodes x-fastest.
 // With RR (kResidual, PO = 5, TE = 2, whole tiles) the residual is not
 // stored: the tile restricts it to 7^3 partial coarse values (RestrictArgs).
-// NT threads per block (one per input column of the z pass: 384 for the
-// 19^2 columns of a p = 6 tile of 2^3 elements).
 template <class T, int PO, int TE, bool RR, int NT = 256>
 __global__ __launch_bounds__(NT) void k_apply(LevelOpT<T> op, const T *__restrict__ x, const T *__restrict__ f,
-                                               T *__restrict__ out, const T *xprev, T *xo, T c1, T c2, int mode,
-                                               double *__restrict__ partial, T s0, RestrictArgs<T> ra,
-                                               const T *__restrict__ cg) {
+                                              T *__restrict__ out, const T *xprev, T *xo, T c1, T c2, int mode,
+                                              double *__restrict__ partial, T s0, RestrictArgs<T> ra) {
   static_assert(!RR || (PO == 5 && TE == 2), "the fused restriction covers p = 5 tiles of 2^3 elements");
   using S = ApplyShape<PO, TE, NT>;
   constexpr int O = S::O, I = S::I;
   static_assert(S::LDS * sizeof(T) >= 256 * sizeof(double), "the dot-product tree reuses the tile");
   __shared__ __align__(16) T lds[S::LDS];  // A, B; then C1, C2, Y; last the dot-product tree
   __shared__ T invd[PO * PO * PO];         // 1 / diag(K) by local node index
-  // x on the owned nodes, from the z-pass columns; p = 6 reads it from global
-  // memory in the epilogue instead (a tile then needs little enough LDS for
-  // two blocks per compute unit)
-  constexpr bool kXoLds = PO != 6;
-  __shared__ T Xo[kXoLds ? O * O * O : 1];
-  // p = 6: the band coefficients (2 x 49 values) come from the device copy
-  // op.cg at wave-uniform addresses (scalar loads); read through the by-value
-  // argument they make the compiler copy the whole operator to scratch
-  // memory, and held in vector registers they spill
-  constexpr bool kGlobalCoef = PO == 6;
+  __shared__ T Xo[O * O * O];              // x on the owned nodes, from the z-pass columns
   T *A = lds;
   T *B = lds + O * S::SA;
   T *C1 = lds;
@@ -339,22 +263,16 @@ __global__ __launch_bounds__(NT) void k_apply(LevelOpT<T> op, const T *__restric
   const bool cheb = (mode == kCheb) || (mode == kChebDot);
   const bool need_f = (mode == kResidual) || cheb || zstart || (mode == kChebZ3);
   const bool need_d = cheb && (c1 != T(0)) && (xprev != nullptr);   // null x_prev reads as zero
-  const bool need_x = !kXoLds && !zstart && (cheb || mode == kChebZ3 || mode == kApplyDot);
   for (int i = tid; i < PO * PO * PO; i += NT) {
     const int kx = i % PO, ky = (i / PO) % PO, kz = i / (PO * PO);
     const T dkx = pick<PO>(op.dk, kx), dky = pick<PO>(op.dk, ky), dkz = pick<PO>(op.dk, kz);
     const T dmx = pick<PO>(op.dm, kx), dmy = pick<PO>(op.dm, ky), dmz = pick<PO>(op.dm, kz);
     invd[i] = T(1) / (dkx * dmy * dmz + dmx * dky * dmz + dmx * dmy * dkz);
   }
-  const T *cme = op.me, *cke = op.ke;
-  if constexpr (kGlobalCoef) {
-    cme = cg;
-    cke = cg + (PO + 1) * (PO + 1);
-  }
   // Addresses: a block-uniform 64-bit tile base plus 32-bit offsets inside
   // the tile (at most O P^2 + O P + O < 2^31 for every supported n).
   const size_t tbase = (size_t(oz0) * P + oy0) * P + ox0;
-  T pf_f[NIT], pf_d[NIT], pf_x[kXoLds ? 1 : NIT];
+  T pf_f[NIT], pf_d[NIT];
 #pragma unroll
   for (int r = 0; r < NIT; ++r) {
     const int li = tid + NT * r;
@@ -363,7 +281,6 @@ __global__ __launch_bounds__(NT) void k_apply(LevelOpT<T> op, const T *__restric
     const size_t g = tbase + unsigned(ok ? (oz * P + oy) * P + ox : 0);
     pf_f[r] = (ok && need_f) ? f[g] : T(0);
     pf_d[r] = (ok && need_d) ? xprev[g] : T(0);
-    if constexpr (!kXoLds) pf_x[r] = (ok && need_x) ? x[g] : T(0);
   }
 
   // pass z
@@ -383,15 +300,15 @@ __global__ __launch_bounds__(NT) void k_apply(LevelOpT<T> op, const T *__restric
 #pragma unroll
       for (int z = 0; z < I; ++z) v[z] *= s0 * id[PO * PO * (z % PO)];
     }
-    if (kXoLds && lx >= PO && lx < PO + O && ly >= PO && ly < PO + O) {
+    if (lx >= PO && lx < PO + O && ly >= PO && ly < PO + O) {
 #pragma unroll
       for (int oz = 0; oz < O; ++oz) Xo[(oz * O + (ly - PO)) * O + (lx - PO)] = v[oz + PO];
     }
     T a[O];
-    band_apply<PO, O>(cme, v, a);
+    band_apply<PO, O>(op.me, v, a);
 #pragma unroll
     for (int oz = 0; oz < O; ++oz) A[oz * S::SA + tid] = a[oz];
-    band_apply<PO, O>(cke, v, a);
+    band_apply<PO, O>(op.ke, v, a);
 #pragma unroll
     for (int oz = 0; oz < O; ++oz) B[oz * S::SA + tid] = a[oz];
   }
@@ -404,11 +321,11 @@ __global__ __launch_bounds__(NT) void k_apply(LevelOpT<T> op, const T *__restric
     T v[I];
 #pragma unroll
     for (int y = 0; y < I; ++y) v[y] = A[oz2 * S::SA + y * I + lx2];
-    band_apply<PO, O>(cme, v, c1v);
-    band_apply<PO, O>(cke, v, c2v);
+    band_apply<PO, O>(op.me, v, c1v);
+    band_apply<PO, O>(op.ke, v, c2v);
 #pragma unroll
     for (int y = 0; y < I; ++y) v[y] = B[oz2 * S::SA + y * I + lx2];
-    band_apply_acc<PO, O>(cme, v, c2v);
+    band_apply_acc<PO, O>(op.me, v, c2v);
   }
   __syncthreads();
   if (act2) {
@@ -425,10 +342,10 @@ __global__ __launch_bounds__(NT) void k_apply(LevelOpT<T> op, const T *__restric
     T v[I], yv[O];
 #pragma unroll
     for (int xx = 0; xx < I; ++xx) v[xx] = C1[oz * S::SC + oy * S::RS + xx];
-    band_apply<PO, O>(cke, v, yv);
+    band_apply<PO, O>(op.ke, v, yv);
 #pragma unroll
     for (int xx = 0; xx < I; ++xx) v[xx] = C2[oz * S::SC + oy * S::RS + xx];
-    band_apply_acc<PO, O>(cme, v, yv);
+    band_apply_acc<PO, O>(op.me, v, yv);
 #pragma unroll
     for (int ox = 0; ox < O; ++ox) Y[(oz * O + oy) * S::YS + ox] = yv[ox];
   }
@@ -493,9 +410,7 @@ __global__ __launch_bounds__(NT) void k_apply(LevelOpT<T> op, const T *__restric
     const int cx = lc % O, cy = (lc / O) % O, cz = lc / (O * O);
     const T y = Y[(cz * O + cy) * S::YS + cx];
     const T id = invd[(ox % PO) + PO * ((oy % PO) + PO * (oz % PO))];
-    T xv;
-    if constexpr (kXoLds) xv = Xo[lc];
-    else xv = zstart ? pf_f[r] * (s0 * id) : pf_x[r];   // the z pass's input: s0 D^-1 f, else x
+    const T xv = Xo[lc];
     const T rr = (pf_f[r] - y) * id;
     T v;
     if (mode == kApply || mode == kApplyDot) v = y;
@@ -514,9 +429,7 @@ __global__ __launch_bounds__(NT) void k_apply(LevelOpT<T> op, const T *__restric
     if (dst[r]) *dst[r] = res[r];
   if (mode == kApplyDot || mode == kChebDot) {
     __syncthreads();  // every thread is done with Y before the tree reuses it
-    double s;
-    if constexpr (NT == 256) s = block_sum(acc, reinterpret_cast<double *>(lds));
-    else s = block_sum_waves(acc, reinterpret_cast<double *>(lds));   // whole waves, not a power of two
+    const double s = block_sum(acc, reinterpret_cast<double *>(lds));
     if (threadIdx.x == 0) partial[blockIdx.x] = s;
   }
 }
@@ -573,13 +486,11 @@ __device__ __forceinline__ void restrict_col(const T *__restrict__ w, const T (&
   }
 }
 
-// NT threads per block, one per fine input column of the z pass (384 for the
-// 18^2 columns of a p = 6 tile of 2^3 coarse elements).
-template <class T, int PF, int PC, int R, int TE, int NT = 256>
-__global__ __launch_bounds__(NT) void k_restrict(TransferT<T> tr, const T *__restrict__ rf, T *__restrict__ fc) {
+template <class T, int PF, int PC, int R, int TE>
+__global__ __launch_bounds__(256) void k_restrict(TransferT<T> tr, const T *__restrict__ rf, T *__restrict__ fc) {
   using S = XferShape<PF, PC, R, TE>;
   constexpr int NS = S::NS, CO = S::CO, NF = S::NF;
-  static_assert(NF * NF <= NT && NF * CO <= NT && CO * CO <= NT, "restriction tile too large");
+  static_assert(NF * NF <= 256 && NF * CO <= 256 && CO * CO <= 256, "restriction tile too large");
   __shared__ T G1[CO * NF * (NF + 1)];   // [cz][fy][fx]
   __shared__ T G2[CO * CO * (NF + 1)];   // [cz][cy][fx]
   __shared__ T Out[CO * CO * CO];        // [cz][cy][cx]
@@ -626,7 +537,7 @@ __global__ __launch_bounds__(NT) void k_restrict(TransferT<T> tr, const T *__res
     for (int c = 0; c < CO; ++c) Out[(cz * CO + cy) * CO + c] = o[c];
   }
   __syncthreads();
-  for (int li = tid; li < CO * CO * CO; li += NT) {
+  for (int li = tid; li < CO * CO * CO; li += 256) {
     const int cx = li % CO, cy = (li / CO) % CO, cz = li / (CO * CO);
     const int gx = tx * CO + cx, gy = ty * CO + cy, gz = tz * CO + cz;
     if (gx < Pc && gy < Pc && gz < Pc) fc[(size_t(gz) * Pc + gy) * Pc + gx] = Out[li];
@@ -1065,14 +976,12 @@ void launch_sub_const(hipStream_t s, int nb, size_t per, double invV, const doub
   hipLaunchKernelGGL(k_sub_const, dim3(nb * K), dim3(256), 0, s, per, K, invV, scal, v);
 }
 
-template <class T, int PO, int TE, int NT = 256>
-static int apply_impl(hipStream_t s, int nb, const LevelOpT<T> &op, const T *x, const T *f, T *out, const T *d, T *xo,
-                      T c1, T c2, int mode, double *partial, T s0) {
-  const int tiles = (op.n + TE - 1) / TE;
-  const int K = tiles * tiles * tiles;
-  if (PO == 6 && !op.cg) return -1;   // the order-6 operator reads its coefficients from op.cg
-  hipLaunchKernelGGL((k_apply<T, PO, TE, false, NT>), dim3(nb * K), dim3(NT), 0, s, op, x, f, out, d, xo, c1, c2,
-                     mode, partial, s0, RestrictArgs<T>{}, op.cg);
+int apply_tiles(int n) { return ((n + 1) / 2) * ((n + 1) / 2) * ((n + 1) / 2); }
+int launch_apply_tiles(hipStream_t s, int nsys, const LevelOp &op, const double *x, double *out, double *partial) {
+  if (op.p != 5) return -1;
+  const int K = apply_tiles(op.n);
+  hipLaunchKernelGGL((k_apply<double, 5, 2, false>), dim3(nsys * K), dim3(256), 0, s, op, x, nullptr, out, nullptr,
+                     nullptr, 0.0, 0.0, int(kApplyDot), partial, 0.0, RestrictArgs<double>{});
   return K;
 }
 
@@ -1112,9 +1021,9 @@ __global__ __launch_bounds__(256) void k_restrict_sum(int Pc, int tiles, int K, 
   }
 }
 
-template <class T>
-int launch_apply_restrict(hipStream_t s, int nb, const LevelOpT<T> &op, const TransferT<T> &tr, const T *x,
-                          const T *f, T *part) {
+int launch_apply_restrict_f32(hipStream_t s, int nb, const LevelOpF &op, const TransferF &tr, const float *x,
+                              const float *f, float *part, float *fc) {
+  using T = float;
   if (op.p != 5 || tr.pf != 5 || tr.pc != 3 || tr.r != 1 || op.n % 2 != 0) return -1;
   RestrictArgs<T> ra{};
   for (int i = 0; i < 20; ++i) ra.w[i] = tr.w[i];
@@ -1122,35 +1031,23 @@ int launch_apply_restrict(hipStream_t s, int nb, const LevelOpT<T> &op, const Tr
   const int tiles = op.n / 2;
   const int K = tiles * tiles * tiles;
   hipLaunchKernelGGL((k_apply<T, 5, 2, true>), dim3(nb * K), dim3(256), 0, s, op, x, f, nullptr, nullptr, nullptr,
-                     T(0), T(0), int(kResidual), nullptr, T(0), ra, op.cg);
+                     T(0), T(0), int(kResidual), nullptr, T(0), ra);
+  const int Pc = 3 * op.n;
+  const int Kr = seg_blocks(nb, size_t(Pc) * Pc * Pc);
+  hipLaunchKernelGGL(k_restrict_sum<T>, dim3(nb * Kr), dim3(256), 0, s, Pc, op.n / 2, Kr, part, fc);
   return K;
 }
 
 template <class T>
-void launch_restrict_sum(hipStream_t s, int nb, int n, const T *part, T *fc) {
-  const int Pc = 3 * n;
-  const int K = seg_blocks(nb, size_t(Pc) * Pc * Pc);
-  hipLaunchKernelGGL(k_restrict_sum<T>, dim3(nb * K), dim3(256), 0, s, Pc, n / 2, K, part, fc);
-}
-
-template <class T>
-int launch_apply(hipStream_t s, int nb, const LevelOpT<T> &op, const T *x, const T *f, T *out, const T *d, T *xo,
-                 T c1, T c2, int mode, double *partial, T s0) {
-  switch (op.p) {
-    case 1: return apply_impl<T, 1, 8>(s, nb, op, x, f, out, d, xo, c1, c2, mode, partial, s0);
-    case 2: return apply_impl<T, 2, 4>(s, nb, op, x, f, out, d, xo, c1, c2, mode, partial, s0);
-    case 3: return apply_impl<T, 3, 4>(s, nb, op, x, f, out, d, xo, c1, c2, mode, partial, s0);
-    case 4: return apply_impl<T, 4, 2>(s, nb, op, x, f, out, d, xo, c1, c2, mode, partial, s0);
-    case 5: return apply_impl<T, 5, 2>(s, nb, op, x, f, out, d, xo, c1, c2, mode, partial, s0);
-    case 6: return apply_impl<T, 6, 2, 384>(s, nb, op, x, f, out, d, xo, c1, c2, mode, partial, s0);
-    default: return -1;
-  }
-}
-
-int apply_blocks(const LevelOp &op) {
-  int TE = op.p == 1 ? 8 : op.p == 2 ? 4 : op.p == 3 ? 4 : 2;
-  int tiles = (op.n + TE - 1) / TE;
-  return tiles * tiles * tiles;
+int launch_apply(hipStream_t s, int nb, int nsys, const LevelOpT<T> &op, const T *x, const T *f, T *out, const T *d,
+                 T *xo, T c1, T c2, int mode, double *partial, T s0) {
+  if (op.p != 1) return launch_march<T>(s, nb, nsys, op, x, f, out, d, xo, c1, c2, mode, partial, s0);
+  constexpr int TE = 8;
+  const int tiles = (op.n + TE - 1) / TE;
+  const int K = tiles * tiles * tiles;
+  hipLaunchKernelGGL((k_apply<T, 1, TE, false>), dim3(nsys * K), dim3(256), 0, s, op, x, f, out, d, xo, c1, c2, mode,
+                     partial, s0, RestrictArgs<T>{});
+  return K;
 }
 
 template <class T>
@@ -1159,10 +1056,10 @@ void launch_cheb_first(hipStream_t s, int nb, const LevelOpT<T> &op, const T *f,
   const int K = seg_blocks(nb, per);
   hipLaunchKernelGGL(k_cheb_first<T>, dim3(nb * K), dim3(256), 0, s, op, K, f, x, c2);
 }
-template <class T, int PF, int PC, int R, int TE, int NT = 256>
+template <class T, int PF, int PC, int R, int TE>
 static void restrict_impl(hipStream_t s, int nb, const TransferT<T> &tr, const T *in, T *out) {
   const int tiles = (tr.nc + TE - 1) / TE;
-  hipLaunchKernelGGL((k_restrict<T, PF, PC, R, TE, NT>), dim3(nb * tiles * tiles * tiles), dim3(NT), 0, s, tr, in,
+  hipLaunchKernelGGL((k_restrict<T, PF, PC, R, TE>), dim3(nb * tiles * tiles * tiles), dim3(256), 0, s, tr, in,
                      out);
 }
 template <class T, int PF, int PC, int R, int TE>
@@ -1172,18 +1069,19 @@ static void prolong_impl(hipStream_t s, int nb, const TransferT<T> &tr, const T 
                      out);
 }
 
-// Supported transfers: p 5 -> 3 and 3 -> 1 on one mesh, Q1 coarsening by 2 or 3.
+// Supported transfers: 5 <-> 3, 4 and 6 <- 3 (their restriction is the
+// operator's, launch_march_restrict) and 3 <-> 1 on one mesh, Q1 coarsening by 2 or 3.
 template <class T>
 int launch_transfer(hipStream_t s, int nb, const TransferT<T> &tr, const T *in, T *out, bool restrict_) {
   if (tr.pf == 5 && tr.pc == 3 && tr.r == 1) {
     if (restrict_) restrict_impl<T, 5, 3, 1, 2>(s, nb, tr, in, out);
-    else prolong_impl<T, 5, 3, 1, 3>(s, nb, tr, in, out);
+    prolong_impl<T, 5, 3, 1, 3>(s, nb, tr, in, out);
   } else if (tr.pf == 4 && tr.pc == 3 && tr.r == 1) {
-    if (restrict_) restrict_impl<T, 4, 3, 1, 2>(s, nb, tr, in, out);
-    else prolong_impl<T, 4, 3, 1, 3>(s, nb, tr, in, out);
+    if (restrict_) return -1;
+    prolong_impl<T, 4, 3, 1, 3>(s, nb, tr, in, out);
   } else if (tr.pf == 6 && tr.pc == 3 && tr.r == 1) {
-    if (restrict_) restrict_impl<T, 6, 3, 1, 2, 384>(s, nb, tr, in, out);
-    else prolong_impl<T, 6, 3, 1, 2>(s, nb, tr, in, out);
+    if (restrict_) return -1;
+    prolong_impl<T, 6, 3, 1, 2>(s, nb, tr, in, out);
   } else if (tr.pf == 3 && tr.pc == 1 && tr.r == 1) {
     if (restrict_) restrict_impl<T, 3, 1, 1, 4>(s, nb, tr, in, out);
     else prolong_impl<T, 3, 1, 1, 5>(s, nb, tr, in, out);
@@ -1204,13 +1102,10 @@ void launch_coarse_solve(hipStream_t s, int nb, int Pn, const double *V, const d
 }
 
 #define FEP3M_MESH_INSTANTIATE(T)                                                                                   \
-  template int launch_apply<T>(hipStream_t, int, const LevelOpT<T> &, const T *, const T *, T *, const T *, T *, T, \
-                               T, int, double *, T);                                                                \
+  template int launch_apply<T>(hipStream_t, int, int, const LevelOpT<T> &, const T *, const T *, T *, const T *, T *, \
+                               T, T, int, double *, T);                                                             \
   template void launch_cheb_first<T>(hipStream_t, int, const LevelOpT<T> &, const T *, T *, T);                     \
   template int launch_transfer<T>(hipStream_t, int, const TransferT<T> &, const T *, T *, bool);                    \
-  template int launch_apply_restrict<T>(hipStream_t, int, const LevelOpT<T> &, const TransferT<T> &, const T *,       \
-                                        const T *, T *);                                                              \
-  template void launch_restrict_sum<T>(hipStream_t, int, int, const T *, T *);                                       \
   template void launch_coarse_solve<T>(hipStream_t, int, int, const double *, const double *, const T *, T *);
 FEP3M_MESH_INSTANTIATE(double)
 FEP3M_MESH_INSTANTIATE(float)

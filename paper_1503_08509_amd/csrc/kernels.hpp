@@ -232,24 +232,35 @@ int launch_mass_dot(hipStream_t s, int nb, int n, int p, const double *w1, const
 void launch_sub_const(hipStream_t s, int nb, size_t per, double invV, const double *scal, double *v);
 // Multigrid kernels in the arithmetic type T (double, or float for the
 // mixed-precision preconditioner); instantiated for both in k_mesh.hip.
-// launch_apply returns its blocks per configuration (the K of kApplyDot);
-// s0 is the first-step coefficient of the kChebZ2 / kChebZ3 modes.
+// launch_apply returns its blocks per system (the K of kApplyDot); nsys
+// systems are applied, nb the configurations of the context (the tiles are
+// chosen for its 2 nb systems, see k_march.hip); s0 is the first-step
+// coefficient of the kChebZ2 / kChebZ3 modes.
 template <class T>
-int launch_apply(hipStream_t s, int nb, const LevelOpT<T> &op, const T *x, const T *f, T *out, const T *xprev, T *xo,
-                 T c1, T c2, int mode, double *partial, T s0 = T(0));
-int apply_blocks(const LevelOp &op);
+int launch_apply(hipStream_t s, int nb, int nsys, const LevelOpT<T> &op, const T *x, const T *f, T *out,
+                 const T *xprev, T *xo, T c1, T c2, int mode, double *partial, T s0 = T(0));
+// the operator of orders 3 to 6 (k_march.hip)
+template <class T>
+int launch_march(hipStream_t s, int nb, int nsys, const LevelOpT<T> &op, const T *x, const T *f, T *out, const T *xprev,
+                 T *xo, T c1, T c2, int mode, double *partial, T s0);
+int march_blocks(int p, int n, int nb);   // its blocks per system
+// Residual f - K x restricted from order 4..6 to order 3 on the same elements
+// without storing it: partial coarse values of each block in part
+// (march_restrict_size values per system), summed into fc.  Returns -1 when
+// the level or the transfer is not such a pair.
+int launch_march_restrict(hipStream_t s, int nb, int nsys, const LevelOp &op, const Transfer &tr, const double *x,
+                          const double *f, double *part, double *fc);
+size_t march_restrict_size(int p, int n, int nb);
+// mixed precision, p = 5: out = K x with x . (K x) partials on tiles of 2^3
+// elements (apply_tiles(n) per system)
+int launch_apply_tiles(hipStream_t s, int nsys, const LevelOp &op, const double *x, double *out, double *partial);
+int apply_tiles(int n);
+// the fused restriction in float32 for p = 5 on the operator tiles of 2^3 elements (n
+// even), 7^3 values per tile in part
+int launch_apply_restrict_f32(hipStream_t s, int nsys, const LevelOpF &op, const TransferF &tr, const float *x,
+                              const float *f, float *part, float *fc);
 template <class T>
 void launch_cheb_first(hipStream_t s, int nb, const LevelOpT<T> &op, const T *f, T *x, T c2);
-// Fine-level residual f - K x restricted from p = 5 to p = 3 without storing
-// it: the operator tiles (2^3 elements, n even) write 7^3 partial coarse
-// values each into part (nb n^3 / 8 * 343 values); launch_restrict_sum adds
-// them into the coarse right side fc.  Returns -1 when the level or the
-// transfer is not the supported pair.
-template <class T>
-int launch_apply_restrict(hipStream_t s, int nb, const LevelOpT<T> &op, const TransferT<T> &tr, const T *x,
-                          const T *f, T *part);
-template <class T>
-void launch_restrict_sum(hipStream_t s, int nb, int n, const T *part, T *fc);
 template <class T>
 int launch_transfer(hipStream_t s, int nb, const TransferT<T> &tr, const T *in, T *out, bool restrict_);
 template <class T>
