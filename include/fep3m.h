@@ -143,8 +143,14 @@ enum {
  * adjoint (Section 3, eq. sc with the Remark's tables).  Both are periodic
  * convolutions over the element lattice with the table as the kernel. */
 enum {
-  FEP3M_NEAR_AUTO = 0,    /* FFT when the mesh allows it (n a power of two,
-                             8 <= n <= 64), else DIRECT                         */
+  FEP3M_NEAR_AUTO = 0,    /* the one-element q = 3 screen on a power of two
+                             8 <= n <= 64: FFT.  Else in float64 up to n = 64,
+                             where n (a box: the lattice padded to n + n_sr or
+                             a little more) is a product of two factors up to
+                             11 or 13: the same maps by mixed-radix transforms,
+                             any screen family, any boundary.  Else (mixed
+                             precision, larger n, a spectrum above 16 GB or
+                             more than memory holds) DIRECT                      */
   FEP3M_NEAR_DIRECT = 1,  /* the table sums themselves: 2 * 8 * (p+1)^3 FLOP per
                              element and near offset (matrix cores forward,
                              vector units for the transpose)                    */
@@ -204,9 +210,10 @@ typedef struct {
                             second stream beside the assignment and the mesh
                             solve; 0: every launch on the caller's stream      */
   int32_t support;       /* FEP3M_SUPPORT_* (default ONE).  Every family but the
-                            one-element q = 3 screen runs in float64 with the
-                            direct near field (matrix cores from 8 moments per
-                            element, vector units for one); create returns
+                            one-element q = 3 screen runs in float64, its near
+                            field by AUTO's transforms or as DIRECT sums
+                            (matrix cores from 8 moments per element, vector
+                            units for one); create returns
                             FEP3M_ERR_UNSUPPORTED for precision = MIXED or
                             near_field = FFT there, and for element orders
                             above 6 (one-element q = 5, 6)                     */
@@ -231,7 +238,9 @@ typedef struct {
   double  tune_ms_best;      /* device time of the chosen variant when tuned      */
   double  tune_ms_default;   /* device time of one wave per element when tuned    */
   int64_t graph_replays;     /* evaluations served by a graph replay (use_graph)  */
-  int32_t near_fft;          /* 1: the near field and its transpose run as FFTs   */
+  int32_t near_fft;          /* 1: the near field and its transpose run as FFTs of
+                                the power-of-two lattice (FEP3M_NEAR_FFT's path;
+                                0 with AUTO's mixed-radix transforms too)         */
   int64_t device_bytes;      /* device memory the context holds                   */
 } fep3m_stats;
 

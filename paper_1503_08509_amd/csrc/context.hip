@@ -185,6 +185,10 @@ struct fep3m_ctx {
   // transformed moments / moment adjoint (4 complex channels), near-screen
   // field and deposits (108 complex channels)
   bool near_fft = false;
+  // the same on lattices of any edge, for the other screen families and for
+  // the boxes (near_field = AUTO, float64)
+  bool conv = false;
+  ConvPlan cv{};
   double2 *spec = nullptr, *twd = nullptr, *zc = nullptr, *za = nullptr, *zpsi = nullptr, *zg = nullptr;
 
   // particles
@@ -406,6 +410,11 @@ struct fep3m_ctx {
   bool std_screen() const { return p == 5 && nl == 2 && span == 1; }
   // moment adjoint in a box (near part from the deposit gE, mesh part from bxlam)
   int box_adjoint_moments() {
+    if (conv) {
+      launch_conv_products(stream, cv, nb, nullptr, gE);
+      launch_conv_adjoint(stream, cv, nb, -1.0, Aadj);
+      return launch_adj_g(stream, nb, n, nsr, p, span, nl, 1, gE, Tt, bxlam, gw, Aadj, nullptr, false);
+    }
     return std_screen() ? launch_adj_moments(stream, nb, p, n, nsr, 1, gE, Tt, bxlam, gw, Aadj)
                         : launch_adj_g(stream, nb, n, nsr, p, span, nl, 1, gE, Tt, bxlam, gw, Aadj);
   }
@@ -413,6 +422,7 @@ struct fep3m_ctx {
   void forward_box(double *Phi, double *U, bool pair_forces);
   void reverse_box(double *F, double *dUdQ);
   void build_near_fft();
+  void build_conv();
   void mesh_solve(double *rhs, double *out, int which, int nsys = 1);
   void adjoint_rhs();
   void store_rel(int which);
@@ -572,6 +582,7 @@ void fep3m_ctx::build(double L_, const std::vector<int64_t> &Ns, int n_, int q_,
   estimate_spectra();
   near_fft = !generic && (opt.near_field == FEP3M_NEAR_FFT || (opt.near_field == FEP3M_NEAR_AUTO && fft_size_ok(n)));
   if (near_fft) build_near_fft();
+  else build_conv();
   stats.near_fft = near_fft ? 1 : 0;
   auto t1 = std::chrono::steady_clock::now();
   stats.create_seconds = std::chrono::duration<double>(t1 - t0).count();
@@ -706,6 +717,47 @@ void fep3m_ctx::build_mg() {
     hip_check(hipMemcpy(coarseV, V.a.data(), V.a.size() * sizeof(double), hipMemcpyHostToDevice), "upload");
     hip_check(hipMemcpy(coarseLam, lam.data(), lam.size() * sizeof(double), hipMemcpyHostToDevice), "upload");
   }
+}
+
+// The convolution's plan, spectrum and work arrays, where near_field = AUTO
+// leaves the choice, in float64 (the table sums of mixed precision are
+// float32).  The table sums stay where the lattice has no plan, where the
+// spectrum would exceed kConvSpecMax (27-element q = 4 screens above 56^3;
+// the others stay below 8 GB at 64^3), and where its memory is not to be had.
+constexpr size_t kConvSpecMax = size_t(16) << 30;
+void fep3m_ctx::build_conv() {
+  if (mixed || opt.near_field != FEP3M_NEAR_AUTO || !conv_plan(n, nsr, p, nl, box, cv)) return;
+  const size_t N3 = size_t(cv.N) * cv.N * cv.N * nb, cc = (cv.na + 1) / 2, cm = (cv.M + 1) / 2;
+  const size_t ns = conv_spec_size(cv);
+  if (ns * sizeof(double2) > kConvSpecMax) return;
+  const size_t want = (ns + N3 * 2 * (cc + cm) + cv.N) * sizeof(double2) + 6 * 512;
+  if (arena && arena_used + want > kStaticBytes) return;
+  const size_t held = allocs.size(), bytes = dev_bytes;
+  try {
+    cv.tw = alloc<double2>(size_t(cv.N), "lattice twiddles");
+    cv.S = alloc<double2>(ns, "table spectrum");
+    cv.zc = alloc<double2>(N3 * cc, "transformed moments");
+    cv.za = alloc<double2>(N3 * cc, "transformed moment adjoint");
+    cv.zpsi = alloc<double2>(N3 * cm, "transformed near-screen field");
+    cv.zg = alloc<double2>(N3 * cm, "transformed deposits");
+  } catch (const Status &e) {
+    if (e.code != FEP3M_ERR_OOM) throw;
+    (void)hipGetLastError();
+    for (size_t i = held; i < allocs.size(); ++i) (void)hipFree(allocs[i]);
+    allocs.resize(held);
+    dev_bytes = bytes;
+    return;
+  }
+  std::vector<double2> tw(cv.N);
+  for (int j = 0; j < cv.N; ++j) {
+    const double t = 2.0 * M_PI * double(j) / double(cv.N);
+    tw[j] = make_double2(std::cos(t), -std::sin(t));
+  }
+  hip_check(hipMemcpy(cv.tw, tw.data(), tw.size() * sizeof(double2), hipMemcpyHostToDevice), "upload twiddles");
+  launch_conv_spec(stream, cv, T);
+  check_launch("table spectrum");
+  hip_check(hipStreamSynchronize(stream), "table spectrum");
+  conv = true;
 }
 
 // Spectrum of the tables at the octant frequencies (create time, on the
@@ -1142,8 +1194,11 @@ void fep3m_ctx::forward_box(double *Phi, double *U, bool pair_forces) {
   stage_mark(FEP3M_PROF_LOAD, false);
   stage_mark(FEP3M_PROF_ASSIGN, false);
   stage_mark(FEP3M_PROF_NEAR, true);
-  // on the matrix cores where the screen family has a kernel there, else by the generic table sums
-  if (launch_psi_mfma_g(stream, nb, n, nsr, p, nl, 1, C, T, nullptr, Wel) != 0 &&
+  // by transforms, else on the matrix cores where the screen family has a kernel there, else by the generic table sums
+  if (conv) {
+    launch_conv_products(stream, cv, nb, C, nullptr);
+    launch_conv_psi(stream, cv, nb, nullptr, Wel);
+  } else if (launch_psi_mfma_g(stream, nb, n, nsr, p, nl, 1, C, T, nullptr, Wel) != 0 &&
       launch_psi_g(stream, nb, n, nsr, p, nl, 1, C, T, nullptr, Wel) != 0)
     throw Status(FEP3M_ERR_UNSUPPORTED, "near field variant");
   stage_mark(FEP3M_PROF_NEAR, false);
@@ -1440,6 +1495,12 @@ void fep3m_ctx::forward(const double *x, const double *Qc, double *Phi, double *
                  : launch_psi_fft_finish<double>(stream, nb, n, p, twd, sol, zpsi, Wel);
     adj_near_ready = pair_forces;
     prof.near_both = pair_forces;
+  } else if (conv) {
+    launch_conv_products(stream, cv, nb, C, pair_forces ? gE : nullptr);
+    launch_conv_psi(stream, cv, nb, sol, Wel);
+    ps = 0;
+    adj_near_ready = pair_forces;
+    prof.near_both = pair_forces;
   } else if (generic) {   // the matrix cores where the family has a kernel there, else the table sums
     ps = launch_psi_mfma_g(stream, nb, n, nsr, p, nl, 0, C, T, sol, Wel);
     if (ps != 0) ps = launch_psi_g(stream, nb, n, nsr, p, nl, 0, C, T, sol, Wel);
@@ -1581,6 +1642,18 @@ void fep3m_ctx::reverse(double *F, double *dUdQ) {
     as = adj_near_ready ? 0 : launch_near_fft(stream, nb, n, p, nullptr, gE, spec, twd, zc, zpsi, zg, za);
     if (as == 0) as = launch_adj_fft_finish(stream, nb, n, p, lam, gw, za, Aadj);
     adj_near_ready = false;
+  } else if (conv) {
+    prof.adj_full = !adj_near_ready;
+    if (!adj_near_ready) launch_conv_products(stream, cv, nb, nullptr, gE);
+    adj_near_ready = false;
+    if (generic) {
+      launch_conv_adjoint(stream, cv, nb, -1.0, Aadj);
+      as = launch_adj_g(stream, nb, n, nsr, p, span, nl, 0, gE, Tt, lam, gw, Aadj, lsep, false);
+    } else {   // the moments' work array holds the near part meanwhile
+      double *B = reinterpret_cast<double *>(cv.zc);
+      launch_conv_adjoint(stream, cv, nb, 1.0, B);
+      as = launch_adj_lambda(stream, nb, n, p, lam, gw, B, Aadj);
+    }
   } else if (generic) {
     as = launch_adj_g(stream, nb, n, nsr, p, span, nl, 0, gE, Tt, lam, gw, Aadj, lsep);
   } else {
@@ -1765,6 +1838,12 @@ void fep3m_ctx::profile_collect() {
   const double S = 2 * nsr + 1;
   const double Me = double(n) * n * n * nb, NM = double(p + 1) * (p + 1) * (p + 1);
   double near_flop = 2.0 * double(na) * NM * S * S * S * Me, adj_work = near_flop;
+  if (conv) {   // operations of the transforms and products that ran
+    const double N3 = double(cv.N) * cv.N * cv.N * nb, dft = 3.0 * 8.0 * (cv.r1 + cv.r2) * N3;
+    const double one = 8.0 * cv.na * cv.M * N3 + dft * 0.5 * (cv.na + cv.M);
+    near_flop = one * (prof.near_both && !box ? 2.0 : 1.0);
+    adj_work = (box || prof.adj_full ? one : 0.0) + dft * 0.25 * cv.na;
+  }
   if (near_fft) {   // bytes in and out of every launch of the FFT pipelines
     const double spec_b = double(spec_freqs(n)) * 8.0 * NM * 16.0;
     const double f4 = Me * 4.0 * 16.0, f108 = Me * NM / 2.0 * 16.0, phi_b = Me * 125.0 * 8.0;

@@ -509,10 +509,15 @@ template int launch_psi_fft_finish<float>(hipStream_t, int, int, int, const doub
 
 int launch_adj_fft_finish(hipStream_t s, int nb, int n, int p, const double *lam, const double *gw, const double2 *za,
                           double *A) {
-  if (p != 5 || !fft_size_ok(n)) return -1;
+  if (!fft_size_ok(n)) return -1;
+  return launch_adj_lambda(s, nb, n, p, lam, gw, reinterpret_cast<const double *>(za), A);
+}
+
+int launch_adj_lambda(hipStream_t s, int nb, int n, int p, const double *lam, const double *gw, const double *Bn,
+                      double *A) {
+  if (p != 5) return -1;
   const size_t ne = size_t(nb) * n * n * n;
-  hipLaunchKernelGGL(k_adj_finish<5>, dim3(unsigned((ne + 255) / 256)), dim3(256), 0, s, n, nb, lam, gw,
-                     reinterpret_cast<const double *>(za), A);
+  hipLaunchKernelGGL(k_adj_finish<5>, dim3(unsigned((ne + 255) / 256)), dim3(256), 0, s, n, nb, lam, gw, Bn, A);
   return 0;
 }
 

@@ -788,7 +788,7 @@ static void adj_near_launch(hipStream_t s, int nb, int n, int nsr, int box, cons
 
 template <int PO, int SPAN>
 static int adj_g_nl(hipStream_t s, int nb, int n, int nsr, int nl, int box, const double *gE, const double *Tt,
-                    const double *lam, const double *gw, double *A, double *sep) {
+                    const double *lam, const double *gw, double *A, double *sep, bool near) {
   if (nsr < 1 || nsr > 3) return -1;
   const int MT = nb * n * n * n;
   if (sep && !box && (SPAN == 3 || nl > 1)) {   // separable lambda part through the load's scratch
@@ -797,7 +797,7 @@ static int adj_g_nl(hipStream_t s, int nb, int n, int nsr, int nl, int box, cons
     const int gz = grid_for_count(int64_t(nb) * n * P * P), gy = grid_for_count(int64_t(nb) * n * n * P);
     const int gx = grid_for_count(int64_t(MT) * nl * nl);
 #define CALL(NL)                                                                                  \
-  adj_near_launch<PO, NL>(s, nb, n, nsr, box, gE, Tt, A);                                         \
+  if (near) adj_near_launch<PO, NL>(s, nb, n, nsr, box, gE, Tt, A);                               \
   hipLaunchKernelGGL((k_adjl_z<PO, SPAN, NL>), dim3(gz), dim3(256), 0, s, nb, n, lam, gw, u1);   \
   hipLaunchKernelGGL((k_adjl_y<PO, SPAN, NL>), dim3(gy), dim3(256), 0, s, nb, n, gw, u1, u2);    \
   hipLaunchKernelGGL((k_adjl_x<PO, SPAN, NL>), dim3(gx), dim3(256), 0, s, nb, n, gw, u2, A)
@@ -807,7 +807,7 @@ static int adj_g_nl(hipStream_t s, int nb, int n, int nsr, int nl, int box, cons
   }
   const int g = grid_for_count(int64_t(MT) * nl * nl * nl);
 #define CALL(NL)                                             \
-  adj_near_launch<PO, NL>(s, nb, n, nsr, box, gE, Tt, A); \
+  if (near) adj_near_launch<PO, NL>(s, nb, n, nsr, box, gE, Tt, A); \
   hipLaunchKernelGGL((k_adj_lam_g<PO, SPAN, NL>), dim3(g), dim3(256), 0, s, n, MT, box, lam, gw, A)
   FEP3M_NL_SWITCH(nl, CALL)
 #undef CALL
@@ -815,22 +815,22 @@ static int adj_g_nl(hipStream_t s, int nb, int n, int nsr, int nl, int box, cons
 }
 
 int launch_adj_g(hipStream_t s, int nb, int n, int nsr, int p, int span, int nl, int box, const double *gE,
-                 const double *T, const double *lam, const double *gw, double *A, double *sep) {
+                 const double *T, const double *lam, const double *gw, double *A, double *sep, bool near) {
   if (box && span != 1) return -1;
   if (span == 1) {
     switch (p) {
-      case 4: return adj_g_nl<4, 1>(s, nb, n, nsr, nl, box, gE, T, lam, gw, A, sep);
-      case 5: return adj_g_nl<5, 1>(s, nb, n, nsr, nl, box, gE, T, lam, gw, A, sep);
-      case 6: return adj_g_nl<6, 1>(s, nb, n, nsr, nl, box, gE, T, lam, gw, A, sep);
+      case 4: return adj_g_nl<4, 1>(s, nb, n, nsr, nl, box, gE, T, lam, gw, A, sep, near);
+      case 5: return adj_g_nl<5, 1>(s, nb, n, nsr, nl, box, gE, T, lam, gw, A, sep, near);
+      case 6: return adj_g_nl<6, 1>(s, nb, n, nsr, nl, box, gE, T, lam, gw, A, sep, near);
       default: return -1;
     }
   }
   if (span == 3) {
     switch (p) {
-      case 3: return adj_g_nl<3, 3>(s, nb, n, nsr, nl, box, gE, T, lam, gw, A, sep);
-      case 4: return adj_g_nl<4, 3>(s, nb, n, nsr, nl, box, gE, T, lam, gw, A, sep);
-      case 5: return adj_g_nl<5, 3>(s, nb, n, nsr, nl, box, gE, T, lam, gw, A, sep);
-      case 6: return adj_g_nl<6, 3>(s, nb, n, nsr, nl, box, gE, T, lam, gw, A, sep);
+      case 3: return adj_g_nl<3, 3>(s, nb, n, nsr, nl, box, gE, T, lam, gw, A, sep, near);
+      case 4: return adj_g_nl<4, 3>(s, nb, n, nsr, nl, box, gE, T, lam, gw, A, sep, near);
+      case 5: return adj_g_nl<5, 3>(s, nb, n, nsr, nl, box, gE, T, lam, gw, A, sep, near);
+      case 6: return adj_g_nl<6, 3>(s, nb, n, nsr, nl, box, gE, T, lam, gw, A, sep, near);
       default: return -1;
     }
   }

@@ -106,7 +106,8 @@ size_t load_sep_scratch(int nb, int n, int p, int nl);
 int launch_psi_g(hipStream_t s, int nb, int n, int nsr, int p, int nl, int box, const double *C, const double *T,
                  const double *phi, double *W);
 int launch_adj_g(hipStream_t s, int nb, int n, int nsr, int p, int span, int nl, int box, const double *gE,
-                 const double *Tt, const double *lam, const double *gw, double *A, double *sep = nullptr);   // Tt: tables as [D][m][a]
+                 const double *Tt, const double *lam, const double *gw, double *A, double *sep = nullptr,
+                 bool near = true);   // Tt: tables as [D][m][a]; near false: A += the lambda part alone
 
 // grounded box (k_box.hip): mesh vectors of (p n + 1)^3 nodes per
 // configuration, P = p n + 1.
@@ -201,6 +202,31 @@ int launch_psi_fft_finish(hipStream_t s, int nb, int n, int p, const double2 *tw
 // A = 4 pi G^T lambda - (near part in za)
 int launch_adj_fft_finish(hipStream_t s, int nb, int n, int p, const double *lam, const double *gw, const double2 *za,
                           double *A);
+
+// the same with the near part B as [E][8] doubles, any n
+int launch_adj_lambda(hipStream_t s, int nb, int n, int p, const double *lam, const double *gw, const double *Bn,
+                      double *A);
+
+// near field and its transpose by transforms of a lattice of any edge
+// N = r1 r2 (factors up to 11 and 13), every screen family, periodic or box
+// (k_conv.hip), float64.  S: conv_spec_size complex values; tw:
+// exp(-2 pi i j / N); work arrays of nb N^3 complex channels: zc, za
+// ceil(na / 2), zpsi, zg ceil(M / 2).
+constexpr int kConvMaxN = 72;
+struct ConvPlan {
+  int n, N, r1, r2, nsr, p, nl, na, M;
+  bool box;
+  double2 *tw, *S, *zc, *za, *zpsi, *zg;
+};
+// false: no plan (n above 64, or a factor above 13)
+bool conv_plan(int n, int nsr, int p, int nl, bool box, ConvPlan &c);
+size_t conv_spec_size(const ConvPlan &c);
+void launch_conv_spec(hipStream_t s, const ConvPlan &c, const double *T);
+// transforms of the moments and / or the deposits, and the products
+void launch_conv_products(hipStream_t s, const ConvPlan &c, int nb, const double *C, const double *gE);
+// W = phi - Psi (null phi: -Psi) from the products; sign * B into A [E][na]
+void launch_conv_psi(hipStream_t s, const ConvPlan &c, int nb, const double *phi, double *W);
+void launch_conv_adjoint(hipStream_t s, const ConvPlan &c, int nb, double sign, double *A);
 
 // exact periodic solve by Fourier analysis over the element lattice
 // (k_fdm.hip): nsys real systems (pairs share one complex work system),
