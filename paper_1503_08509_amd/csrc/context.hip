@@ -397,6 +397,10 @@ struct fep3m_ctx {
   void backward(int64_t gen, double *F, double *dUdQ);
   void build_mg();
   void estimate_spectra();
+  int q1_from = -1;          // first level of the one-launch cycle (float64), or none
+  Q1Cycle q1{};
+  void build_q1();
+  void cheb_coefs(int l, double *c1, double *c2) const;
   template <class T> int vcycle(int l, const T *f, double *dot_part = nullptr);
   template <class T> int cheb_smooth(int l, const T *f, bool zero_start, double *dot_part = nullptr);
   void solve(const double *rhs, double *out, int which);
@@ -580,6 +584,7 @@ void fep3m_ctx::build(double L_, const std::vector<int64_t> &Ns, int n_, int q_,
   partial_len = std::max(partial_len, size_t(kRowBlocks) + 64);
   partial = alloc<double>(partial_len, "partials");
   estimate_spectra();
+  build_q1();
   near_fft = !generic && (opt.near_field == FEP3M_NEAR_FFT || (opt.near_field == FEP3M_NEAR_AUTO && fft_size_ok(n)));
   if (near_fft) build_near_fft();
   else build_conv();
@@ -893,6 +898,46 @@ void fep3m_ctx::estimate_spectra() {
 
 // ----------------------------------------------------------------- multigrid
 
+// Coefficients of the Chebyshev steps on level l (x + c1 (x - x_prev) + c2
+// D^-1 (f - K x); c1 = 0 in the first) for the interval [lmax / 12, 1.1 lmax].
+void fep3m_ctx::cheb_coefs(int l, double *c1, double *c2) const {
+  const double bmax = 1.1 * lv[l].lmax, amin = bmax / 12.0;
+  const double theta = 0.5 * (bmax + amin), delta = 0.5 * (bmax - amin), sigma = theta / delta;
+  double rho = 1.0 / sigma;
+  c1[0] = 0.0;
+  c2[0] = 1.0 / theta;
+  for (int s = 1; s < opt.cheb_degree; ++s) {
+    const double rn = 1.0 / (2.0 * sigma - rho);
+    c1[s] = rn * rho;
+    c2[s] = 2.0 * rn / delta;
+    rho = rn;
+  }
+}
+
+// The order-1 levels from kQ1Max elements per axis down go through one launch
+// where they fit its LDS and there are at least two of them.
+void fep3m_ctx::build_q1() {
+  if (mixed) return;
+  for (size_t l = 0; l + 1 < lv.size(); ++l) {
+    if (lv[l].op.p != 1 || lv[l].op.n > kQ1Max || lv.size() - l > size_t(kQ1Levels)) continue;
+    q1 = Q1Cycle{};
+    q1.levels = int(lv.size() - l);
+    q1.deg = opt.cheb_degree;
+    q1.V = coarseV;
+    q1.lam = coarseLam;
+    for (int k = 0; k < q1.levels; ++k) {
+      q1.lv[k] = q1_level(lv[l + k].op);
+      if (k + 1 < q1.levels) cheb_coefs(int(l) + k, q1.lv[k].c1, q1.lv[k].c2);
+    }
+    q1.nlast = q1.lv[q1.levels - 1].n;
+    q1.f_lds = true;
+    if (q1_cycle_lds(q1) > 160 * 1024) q1.f_lds = false;
+    if (q1_cycle_lds(q1) > 160 * 1024) continue;
+    q1_from = int(l);
+    return;
+  }
+}
+
 // Chebyshev(deg)-Jacobi smoothing on level l in arithmetic type T, targeting
 // the interval [lmax / 12, 1.1 lmax] of D^-1 K.
 // With dot_part, the last step also writes block partials of x_new . f
@@ -903,22 +948,12 @@ int fep3m_ctx::cheb_smooth(int l, const T *f, bool zero_start, double *dot_part)
   MGLevel &L_ = lv[l];
   LevelVecs<T> &V = L_.vec<T>();
   const LevelOpT<T> &op = L_.oper<T>();
-  const double bmax = 1.1 * L_.lmax, amin = bmax / 12.0;
-  const double theta = 0.5 * (bmax + amin), delta = 0.5 * (bmax - amin), sigma = theta / delta;
-  double rho = 1.0 / sigma;
   const int deg = opt.cheb_degree;
+  double c1s[kQ1Deg], c2s[kQ1Deg];
+  cheb_coefs(l, c1s, c2s);
   double s0 = 0.0;   // first-step coefficient: x1 = s0 D^-1 f after a zero start
   for (int s = 0; s < deg; ++s) {
-    double c1, c2;
-    if (s == 0) {
-      c1 = 0.0;
-      c2 = 1.0 / theta;
-    } else {
-      const double rn = 1.0 / (2.0 * sigma - rho);
-      c1 = rn * rho;
-      c2 = 2.0 * rn / delta;
-      rho = rn;
-    }
+    const double c1 = c1s[s], c2 = c2s[s];
     if (s == 0 && zero_start) {
       s0 = c2;
       // with later steps, the operator rebuilds x1 from f where it needs it
@@ -950,6 +985,12 @@ template <class T>
 int fep3m_ctx::vcycle(int l, const T *f, double *dot_part) {
   MGLevel &L_ = lv[l];
   LevelVecs<T> &V = L_.vec<T>();
+  if constexpr (sizeof(T) == 8) {
+    if (l == q1_from) {
+      launch_q1_cycle(stream, nbs, q1, f, V.x);
+      return 0;
+    }
+  }
   if (l + 1 == int(lv.size())) {
     launch_coarse_solve<T>(stream, nbs, coarseP, coarseV, coarseLam, f, V.x);
     return 0;
@@ -1311,16 +1352,18 @@ void fep3m_ctx::solve(const double *rhs, double *sol, int which) {
   // loop.
   const double *rcur = rhs;
   bool xinit = false;
-  // z = M^-1 r; rzn = z . r (and zq = z . q when q is given)
-  auto precondition = [&](const double *q) {
+  // z = M^-1 r; rzn = z . r (and zq = z . q when q is given), then the step of
+  // the scalars that follows
+  auto precondition = [&](const double *q, int step) {
     if (!mixed) {   // z . r from the V-cycle's last smoothing step
-      launch_sum_partials(stream, vcycle<double>(0, rcur, partial), partial, pcs.rzn, nbs);
+      const int K = vcycle<double>(0, rcur, partial);
+      launch_pcg_reduce(stream, nbs, K, partial, pcs.rzn, step, 0.0, pcs);
     } else {
       if (!q) launch_to_f32(stream, nd, rcur, L0.vf.f);   // later residuals come with their float copy
       vcycle<float>(0, L0.vf.f);
       const int K = launch_dot2_f32(stream, nbs, per, L0.vf.x, rcur, q, dot_scr);
-      launch_sum_partials(stream, K, dot_scr, pcs.rzn, nbs);
       launch_sum_partials(stream, K, dot_scr + size_t(nbs) * K, pcs.zq, nbs);
+      launch_pcg_reduce(stream, nbs, K, dot_scr, pcs.rzn, step, 0.0, pcs);
     }
   };
   auto set_p = [&] {   // x += alpha p (deferred); p = z + beta p
@@ -1328,8 +1371,7 @@ void fep3m_ctx::solve(const double *rhs, double *sol, int which) {
     else launch_xp_update<float>(stream, nbs, per, pcs.alpha, pcs.beta, L0.vf.x, pv, sol, xinit);
     xinit = true;
   };
-  precondition(nullptr);
-  launch_pcg_scalars(stream, nbs, kPcgStart, 0.0, pcs);   // act = (b != 0), beta = 0, rz = z . r
+  precondition(nullptr, kPcgStart);   // act = (b != 0), beta = 0, rz = z . r
   if (!mixed) launch_p_init<double>(stream, nbs, per, L0.vd.x, pv);
   else launch_p_init<float>(stream, nbs, per, L0.vf.x, pv);
   // Eagerly, the host reads the residuals after every iteration and stops
@@ -1342,12 +1384,10 @@ void fep3m_ctx::solve(const double *rhs, double *sol, int which) {
   int it = 0;
   for (it = 1; it <= opt.mg_max_iter; ++it) {
     const int Ka = apply0<double>(pv, nullptr, qv, nullptr, nullptr, 0.0, 0.0, kApplyDot, partial);
-    launch_sum_partials(stream, Ka, partial, pcs.pq, nbs);
-    launch_pcg_scalars(stream, nbs, kPcgAlpha, 0.0, pcs);
-    launch_sum_partials(stream, launch_r_update(stream, nbs, per, pcs.alpha, qv, rcur, rr, partial,
-                                                mixed ? L0.vf.f : nullptr), partial, pcs.rr, nbs);
+    launch_pcg_reduce(stream, nbs, Ka, partial, pcs.pq, kPcgAlpha, 0.0, pcs);
+    const int Kr = launch_r_update(stream, nbs, per, pcs.alpha, qv, rcur, rr, partial, mixed ? L0.vf.f : nullptr);
+    launch_pcg_reduce(stream, nbs, Kr, partial, pcs.rr, kPcgResid, opt.mg_rtol, pcs);
     rcur = rr;
-    launch_pcg_scalars(stream, nbs, kPcgResid, opt.mg_rtol, pcs);
     if (capturing) {
       if (it >= fixed) break;
     } else {
@@ -1358,8 +1398,7 @@ void fep3m_ctx::solve(const double *rhs, double *sol, int which) {
       for (int bb = 0; bb < nbs; ++bb) relmax = std::max(relmax, host_cs[bb]);
       if (relmax <= opt.mg_rtol) break;
     }
-    precondition(qv);
-    launch_pcg_scalars(stream, nbs, mixed ? kPcgBetaPR : kPcgBeta, 0.0, pcs);
+    precondition(qv, mixed ? kPcgBetaPR : kPcgBeta);
     set_p();
   }
   // the loop left through its break (converged, or the captured count):

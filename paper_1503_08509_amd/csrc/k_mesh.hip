@@ -867,44 +867,43 @@ __global__ __launch_bounds__(256) void k_dot2_f32(size_t per, int K, const float
   }
 }
 
-// PCG scalars, one thread per configuration, on arrays of nb values:
+// One step of the PCG scalars of system b:
 //   kPcgStart  act = (bn2 > 0); beta = 0; rz = rzn
 //   kPcgAlpha  alpha = act ? rz / pq : 0
 //   kPcgResid  rel = sqrt(rr) / sqrt(bn2) (0 if bn2 = 0); act &= rel > rtol
 //   kPcgBeta   beta = act ? rzn / rz : 0; rz = rzn
 //   kPcgBetaPR beta = act ? -alpha zq / rz : 0; rz = rzn (flexible form)
-__global__ __launch_bounds__(64) void k_pcg_scalars(int nb, int step, double rtol, PcgScalars s) {
-  for (int b = threadIdx.x; b < nb; b += blockDim.x) {
-    switch (step) {
-      case kPcgStart:
-        s.act[b] = s.bn2[b] > 0.0 ? 1.0 : 0.0;
-        s.beta[b] = 0.0;
-        s.rz[b] = s.rzn[b];
-        break;
-      case kPcgAlpha: s.alpha[b] = s.act[b] != 0.0 ? s.rz[b] / s.pq[b] : 0.0; break;
-      case kPcgResid: {
-        const double rel = s.bn2[b] > 0.0 ? sqrt(s.rr[b]) / sqrt(s.bn2[b]) : 0.0;
-        s.rel[b] = rel;
-        if (!(rel > rtol)) s.act[b] = 0.0;
-        break;
-      }
-      case kPcgBeta:
-        s.beta[b] = s.act[b] != 0.0 ? s.rzn[b] / s.rz[b] : 0.0;
-        s.rz[b] = s.rzn[b];
-        break;
-      default:
-        s.beta[b] = s.act[b] != 0.0 ? -s.alpha[b] * s.zq[b] / s.rz[b] : 0.0;
-        s.rz[b] = s.rzn[b];
-        break;
+__device__ __forceinline__ void pcg_step(int b, int step, double rtol, const PcgScalars &s) {
+  switch (step) {
+    case kPcgStart:
+      s.act[b] = s.bn2[b] > 0.0 ? 1.0 : 0.0;
+      s.beta[b] = 0.0;
+      s.rz[b] = s.rzn[b];
+      break;
+    case kPcgAlpha: s.alpha[b] = s.act[b] != 0.0 ? s.rz[b] / s.pq[b] : 0.0; break;
+    case kPcgResid: {
+      const double rel = s.bn2[b] > 0.0 ? sqrt(s.rr[b]) / sqrt(s.bn2[b]) : 0.0;
+      s.rel[b] = rel;
+      if (!(rel > rtol)) s.act[b] = 0.0;
+      break;
     }
+    case kPcgBeta:
+      s.beta[b] = s.act[b] != 0.0 ? s.rzn[b] / s.rz[b] : 0.0;
+      s.rz[b] = s.rzn[b];
+      break;
+    default:
+      s.beta[b] = s.act[b] != 0.0 ? -s.alpha[b] * s.zq[b] / s.rz[b] : 0.0;
+      s.rz[b] = s.rzn[b];
+      break;
   }
+}
+__global__ __launch_bounds__(64) void k_pcg_scalars(int nb, int step, double rtol, PcgScalars s) {
+  for (int b = threadIdx.x; b < nb; b += blockDim.x) pcg_step(b, step, rtol, s);
 }
 
 // Second stage of every reduction: block b sums the K partials of
 // configuration b in a fixed order into out[b].
-__global__ __launch_bounds__(256) void k_sum_partials(int K, const double *__restrict__ partial, double *__restrict__ out) {
-  __shared__ double red[256];
-  partial += size_t(blockIdx.x) * K;
+__device__ __forceinline__ double sum_partials(int K, const double *__restrict__ partial, double *red) {
   // eight independent sums per thread keep eight loads in flight (one block
   // may read tens of thousands of partials); fixed order, so repeatable
   double a[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -915,8 +914,24 @@ __global__ __launch_bounds__(256) void k_sum_partials(int K, const double *__res
   }
   for (; i < K; i += 256) a[0] += partial[i];
   const double acc = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-  double t = block_sum(acc, red);
+  return block_sum(acc, red);
+}
+__global__ __launch_bounds__(256) void k_sum_partials(int K, const double *__restrict__ partial, double *__restrict__ out) {
+  __shared__ double red[256];
+  const double t = sum_partials(K, partial + size_t(blockIdx.x) * K, red);
   if (threadIdx.x == 0) out[blockIdx.x] = t;
+}
+// The same, then the system's step of the PCG scalars (it reads no other
+// system's): one launch instead of two, three times per iteration (5 us each
+// while a small solve's iteration takes 150).
+__global__ __launch_bounds__(256) void k_pcg_reduce(int K, const double *__restrict__ partial, double *__restrict__ out,
+                                                    int step, double rtol, PcgScalars s) {
+  __shared__ double red[256];
+  const double t = sum_partials(K, partial + size_t(blockIdx.x) * K, red);
+  if (threadIdx.x == 0) {
+    out[blockIdx.x] = t;
+    pcg_step(blockIdx.x, step, rtol, s);
+  }
 }
 
 // ----------------------------------------------------------------- launchers
@@ -1119,6 +1134,10 @@ int launch_dot2_f32(hipStream_t s, int nb, size_t per, const float *z, const dou
   const int K = seg_blocks(nb, per);
   hipLaunchKernelGGL(k_dot2_f32, dim3(nb * K), dim3(256), 0, s, per, K, z, r, q, partial);
   return K;
+}
+void launch_pcg_reduce(hipStream_t s, int nb, int K, const double *partial, double *out, int step, double rtol,
+                       const PcgScalars &sc) {
+  hipLaunchKernelGGL(k_pcg_reduce, dim3(nb), dim3(256), 0, s, K, partial, out, step, rtol, sc);
 }
 void launch_pcg_scalars(hipStream_t s, int nb, int step, double rtol, const PcgScalars &sc) {
   hipLaunchKernelGGL(k_pcg_scalars, dim3(1), dim3(64), 0, s, nb, step, rtol, sc);

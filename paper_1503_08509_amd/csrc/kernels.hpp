@@ -291,10 +291,31 @@ template <class T>
 int launch_transfer(hipStream_t s, int nb, const TransferT<T> &tr, const T *in, T *out, bool restrict_);
 template <class T>
 void launch_coarse_solve(hipStream_t s, int nb, int Pn, const double *V, const double *lam, const T *f, T *x);
+// The cycle from an order-1 level of at most kQ1Max elements per axis down, in
+// one launch (k_q1cycle.hip), float64: x from zero for K x = f, nsys systems.
+constexpr int kQ1Max = 20, kQ1Levels = 4, kQ1Deg = 10;
+struct Q1Level {
+  int n;
+  double st[4], invd;                    // operator by number of axes off the node, inverse diagonal
+  double c1[kQ1Deg], c2[kQ1Deg];         // Chebyshev steps
+};
+struct Q1Cycle {
+  int levels, deg;
+  int nlast;                             // edge of the last level
+  bool f_lds;                            // the first level's right side in LDS too
+  Q1Level lv[kQ1Levels];                 // the last one is solved exactly
+  const double *V, *lam;                 // its one-dimensional eigenbasis
+};
+Q1Level q1_level(const LevelOp &op);     // c1, c2 left to the caller
+size_t q1_cycle_lds(const Q1Cycle &q);   // LDS bytes it takes
+void launch_q1_cycle(hipStream_t s, int nsys, const Q1Cycle &q, const double *f, double *x);
 void launch_to_f32(hipStream_t s, size_t n, const double *a, float *b);
 // partial[0, nb K): block sums of z.r; partial[nb K, 2 nb K): z.q (0 if q is null); returns K
 int launch_dot2_f32(hipStream_t s, int nb, size_t per, const float *z, const double *r, const double *q,
                     double *partial);
+// out = the partials' sums, then the step
+void launch_pcg_reduce(hipStream_t s, int nb, int K, const double *partial, double *out, int step, double rtol,
+                       const PcgScalars &sc);
 void launch_pcg_scalars(hipStream_t s, int nb, int step, double rtol, const PcgScalars &sc);
 int launch_dot(hipStream_t s, int nb, size_t per, const double *a, const double *b, double *partial);
 // PCG updates.  r_out = r_in - alpha q with block partials of r_out . r_out
