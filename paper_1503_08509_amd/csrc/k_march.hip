@@ -674,42 +674,38 @@ int march(hipStream_t s, int nb, int nsys, const LevelOpT<T> &op, const Transfer
 // Partial coarse values summed per coarse node (order 3): those of its own
 // block and, for a node on the block's lower faces, the upper vertex values
 // of the blocks below, in a fixed order.
-__global__ __launch_bounds__(256) void k_march_restrict_sum(MarchPlan pl, int n, int K,
-                                                            const double *__restrict__ partall,
+// One row of coarse nodes per block, so that only x is worked out per node
+// (123 us at 64^3, two systems, with all three indices per node; 85 us).
+__global__ __launch_bounds__(256) void k_march_restrict_sum(MarchPlan pl, int n, const double *__restrict__ partall,
                                                             double *__restrict__ fcall) {
-  using T = double;
-  const int Pc = 3 * n;
-  const size_t total = size_t(Pc) * Pc * Pc;
-  const int cfg = blockIdx.x / K, kb = blockIdx.x % K;
+  const int Pc = 3 * n, gy = blockIdx.x % Pc, gz = blockIdx.x / Pc % Pc, cfg = blockIdx.x / Pc / Pc;
   const int cx = 3 * pl.tx + 1, cy = 3 * pl.ty + 1, cz = 3 * pl.ze + 1;
-  const T *part = partall + size_t(cfg) * pl.blocks() * cx * cy * cz;
-  T *fc = fcall + size_t(cfg) * total;
-  const int te[3] = {pl.tx, pl.ty, pl.ze}, nt[3] = {pl.nx, pl.ny, pl.nz};
-  for (size_t g = size_t(kb) * blockDim.x + threadIdx.x; g < total; g += size_t(K) * blockDim.x) {
-    const unsigned u = unsigned(g), gyz = u / unsigned(Pc);
-    const int gg[3] = {int(u - gyz * unsigned(Pc)), int(gyz % unsigned(Pc)), int(gyz / unsigned(Pc))};
-    int t[3][2], k[3][2], nn[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      const int w = 3 * te[a];
-      t[a][0] = gg[a] / w;
-      k[a][0] = gg[a] - t[a][0] * w;
-      nn[a] = 1;
-      if (k[a][0] == 0) {
-        t[a][1] = t[a][0] == 0 ? nt[a] - 1 : t[a][0] - 1;
-        // the last block of an axis may hold fewer elements
-        k[a][1] = t[a][0] == 0 ? 3 * (n - te[a] * (nt[a] - 1)) : w;
-        nn[a] = 2;
+  const double *part = partall + size_t(cfg) * pl.blocks() * cx * cy * cz;
+  double *fc = fcall + ((size_t(cfg) * Pc + gz) * Pc + gy) * Pc;
+  // blocks (one or two) that hold coarse node g of an axis and its index in them
+  auto owners = [n](int g, int te, int nt, int(&t)[2], int(&k)[2]) {
+    const int w = 3 * te;
+    t[0] = g / w;
+    k[0] = g - t[0] * w;
+    if (k[0] != 0) return 1;
+    t[1] = t[0] == 0 ? nt - 1 : t[0] - 1;
+    k[1] = t[0] == 0 ? 3 * (n - te * (nt - 1)) : w;   // the last block of an axis may hold fewer elements
+    return 2;
+  };
+  int ty[2], ky[2], tz[2], kz[2];
+  const int ny = owners(gy, pl.ty, pl.ny, ty, ky), nz = owners(gz, pl.ze, pl.nz, tz, kz);
+  for (int gx = threadIdx.x; gx < Pc; gx += blockDim.x) {
+    int tx[2], kx[2];
+    const int nx = owners(gx, pl.tx, pl.nx, tx, kx);
+    double s = 0.0;
+    for (int iz = 0; iz < nz; ++iz)
+      for (int iy = 0; iy < ny; ++iy) {
+        const size_t row = size_t(tz[iz] * pl.ny + ty[iy]) * pl.nx;
+        const int at = (kz[iz] * cy + ky[iy]) * cx;
+        s += part[(row + tx[0]) * (cx * cy * cz) + at + kx[0]];
+        if (nx == 2) s += part[(row + tx[1]) * (cx * cy * cz) + at + kx[1]];
       }
-    }
-    T s = T(0);
-    for (int iz = 0; iz < nn[2]; ++iz)
-      for (int iy = 0; iy < nn[1]; ++iy)
-        for (int ix = 0; ix < nn[0]; ++ix) {
-          const size_t tile = (size_t(t[2][iz]) * pl.ny + t[1][iy]) * pl.nx + t[0][ix];
-          s += part[((tile * cz + k[2][iz]) * cy + k[1][iy]) * cx + k[0][ix]];
-        }
-    fc[g] = s;
+    fc[gx] = s;
   }
 }
 
@@ -734,9 +730,9 @@ int launch_march_restrict(hipStream_t s, int nb, int nsys, const LevelOp &op, co
   const int K = march<double>(s, nb, nsys, op, &tr, x, f, part, nullptr, nullptr, 0.0, 0.0, kResidualRestrict, nullptr,
                               0.0);
   if (K < 0) return K;
-  const int Kr = seg_blocks(nsys, size_t(27) * op.n * op.n * op.n);
-  hipLaunchKernelGGL(k_march_restrict_sum, dim3(nsys * Kr), dim3(256), 0, s, march_plan(op.p, op.n, nb), op.n, Kr, part,
-                     fc);
+  const int Pc = 3 * op.n;
+  hipLaunchKernelGGL(k_march_restrict_sum, dim3(unsigned(nsys) * Pc * Pc), dim3(Pc >= 256 ? 256 : 64 * ((Pc + 63) / 64)), 0,
+                     s, march_plan(op.p, op.n, nb), op.n, part, fc);
   return K;
 }
 

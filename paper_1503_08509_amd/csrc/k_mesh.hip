@@ -1084,22 +1084,16 @@ static void prolong_impl(hipStream_t s, int nb, const TransferT<T> &tr, const T 
                      out);
 }
 
-// Supported transfers: 5 <-> 3, 4 and 6 <- 3 (their restriction is the
-// operator's, launch_march_restrict) and 3 <-> 1 on one mesh, Q1 coarsening by 2 or 3.
+// Supported transfers: prolongation 5, 4, 6 from 3 and 3 from 1 on one mesh
+// (k_prolong.hip), Q1 coarsening by 2 or 3; restriction 5 to 3 (the others'
+// is the operator's, launch_march_restrict), 3 to 1, Q1 by 2 or 3.
 template <class T>
 int launch_transfer(hipStream_t s, int nb, const TransferT<T> &tr, const T *in, T *out, bool restrict_) {
+  if (tr.r == 1 && !restrict_) return launch_prolong<T>(s, nb, tr, in, out);
   if (tr.pf == 5 && tr.pc == 3 && tr.r == 1) {
-    if (restrict_) restrict_impl<T, 5, 3, 1, 2>(s, nb, tr, in, out);
-    prolong_impl<T, 5, 3, 1, 3>(s, nb, tr, in, out);
-  } else if (tr.pf == 4 && tr.pc == 3 && tr.r == 1) {
-    if (restrict_) return -1;
-    prolong_impl<T, 4, 3, 1, 3>(s, nb, tr, in, out);
-  } else if (tr.pf == 6 && tr.pc == 3 && tr.r == 1) {
-    if (restrict_) return -1;
-    prolong_impl<T, 6, 3, 1, 2>(s, nb, tr, in, out);
+    restrict_impl<T, 5, 3, 1, 2>(s, nb, tr, in, out);
   } else if (tr.pf == 3 && tr.pc == 1 && tr.r == 1) {
-    if (restrict_) restrict_impl<T, 3, 1, 1, 4>(s, nb, tr, in, out);
-    else prolong_impl<T, 3, 1, 1, 5>(s, nb, tr, in, out);
+    restrict_impl<T, 3, 1, 1, 4>(s, nb, tr, in, out);
   } else if (tr.pf == 1 && tr.pc == 1 && tr.r == 2) {
     if (restrict_) restrict_impl<T, 1, 1, 2, 7>(s, nb, tr, in, out);
     else prolong_impl<T, 1, 1, 2, 8>(s, nb, tr, in, out);

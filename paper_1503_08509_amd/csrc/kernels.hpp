@@ -287,6 +287,9 @@ int launch_apply_restrict_f32(hipStream_t s, int nsys, const LevelOpF &op, const
                               const float *f, float *part, float *fc);
 template <class T>
 void launch_cheb_first(hipStream_t s, int nb, const LevelOpT<T> &op, const T *f, T *x, T c2);
+// xf += P ec between orders on one mesh (k_prolong.hip)
+template <class T>
+int launch_prolong(hipStream_t s, int nsys, const TransferT<T> &tr, const T *in, T *out);
 template <class T>
 int launch_transfer(hipStream_t s, int nb, const TransferT<T> &tr, const T *in, T *out, bool restrict_);
 template <class T>
