@@ -425,7 +425,10 @@ __global__ __launch_bounds__(64) void k_pair_queue(int n, int64_t N, const int *
 
 // Phi_m at each sorted charge: sum_m W_E[m] u_m(u_i) (W = phi - Psi of its
 // element, element units) by sum factorisation; then the combined
-// potential (Phi_p + Phi_m) / h, scattered to caller order.
+// potential (Phi_p + Phi_m) / h, scattered to caller order.  Eight lanes per
+// charge (four at order 3), lane k node plane k: bound by the lines that W's
+// rows touch.  One lane per charge left a chain of 216 loads: 13 us for 1000
+// charges and 219 for 10^6 on 64^3; 4 and 180 us so.
 template <int PO>
 __global__ __launch_bounds__(256) void k_interp(int n, int64_t N, int nb, const int *__restrict__ off, double inv_h,
                                                 GllBasis bas, const double *__restrict__ sg,
@@ -433,9 +436,11 @@ __global__ __launch_bounds__(256) void k_interp(int n, int64_t N, int nb, const 
                                                 const double *__restrict__ phip, const int *__restrict__ perm,
                                                 double *__restrict__ phim_s, double *__restrict__ phi_s,
                                                 double *__restrict__ Phi) {
-  constexpr int Q1 = PO + 1;
-  for (int64_t s = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; s < N; s += int64_t(gridDim.x) * blockDim.x) {
-    double l[3][Q1];
+  constexpr int Q1 = PO + 1, LN = Q1 <= 4 ? 4 : 8;
+  const int mz = threadIdx.x % LN;
+  const int64_t step = int64_t(gridDim.x) * (256 / LN);
+  for (int64_t s = int64_t(blockIdx.x) * (256 / LN) + threadIdx.x / LN; s < N; s += step) {   // all lanes of a charge agree
+    double l[2][Q1], lz = 0.0;
     int e[3];
     for (int k = 0; k < 3; ++k) {
       const double g = sg[k * N + s];
@@ -449,29 +454,30 @@ __global__ __launch_bounds__(256) void k_interp(int n, int64_t N, int nb, const 
 #pragma unroll
         for (int j = 0; j < Q1; ++j)
           if (j != a) v *= (u - bas.x[j]);
-        l[k][a] = v;
+        if (k < 2) l[k & 1][a] = v;
+        else if (a == mz) lz = v;
       }
     }
     const size_t E = size_t(cfg_of(off, nb, s)) * n * n * n + size_t(e[0]) + size_t(n) * (e[1] + size_t(n) * e[2]);
-    const double *w = Wel + E * (Q1 * Q1 * Q1);
-    double acc = 0.0;
+    const double *w = Wel + E * (Q1 * Q1 * Q1) + (mz < Q1 ? mz : 0) * Q1 * Q1;
+    double sy = 0.0;
 #pragma unroll
-    for (int mz = 0; mz < Q1; ++mz) {
-      double sy = 0.0;
+    for (int my = 0; my < Q1; ++my) {
+      double sx = 0.0;
 #pragma unroll
-      for (int my = 0; my < Q1; ++my) {
-        double sx = 0.0;
-#pragma unroll
-        for (int mx = 0; mx < Q1; ++mx) sx += l[0][mx] * w[(mz * Q1 + my) * Q1 + mx];
-        sy += l[1][my] * sx;
-      }
-      acc += l[2][mz] * sy;
+      for (int mx = 0; mx < Q1; ++mx) sx += l[0][mx] * w[my * Q1 + mx];
+      sy += l[1][my] * sx;
     }
-    const double pm = acc * inv_h;
-    const double tot = phip[s] * inv_h + pm;
-    phim_s[s] = pm;
-    phi_s[s] = tot;
-    Phi[perm[s]] = tot;
+    double acc = lz * sy;   // lz = 0 in the lanes past the last plane
+#pragma unroll
+    for (int o = 1; o < LN; o <<= 1) acc += __shfl_xor(acc, o, 64);
+    if (mz == 0) {
+      const double pm = acc * inv_h;
+      const double tot = phip[s] * inv_h + pm;
+      phim_s[s] = pm;
+      phi_s[s] = tot;
+      Phi[perm[s]] = tot;
+    }
   }
 }
 
@@ -501,24 +507,39 @@ __global__ __launch_bounds__(256) void k_unpermute(int64_t N, double scale, cons
 }
 
 // Ordered near pairs: sum_E count_E * (sum over the block of counts) - N.
+// Eight lanes per element, lane k its block's layer k - NSR (NSR 4: lane 0
+// the last one too); a row of elements is one or two runs of sorted charges.
+// One atomic per block and at most 512 blocks: they queue on one address, 13
+// ns each.  14 us on 16^3 elements and 88 on 64^3 with one thread per
+// element, 5 and 60 so.
 template <int NSR>
 __global__ __launch_bounds__(256) void k_pair_count(int n, int MT, const int *__restrict__ start,
                                                     unsigned long long *__restrict__ out) {
-  const int M = n * n * n;
-  for (int E = blockIdx.x * blockDim.x + threadIdx.x; E < MT; E += gridDim.x * blockDim.x) {
-    const int c = start[E + 1] - start[E];
-    if (c == 0) continue;
+  const int M = n * n * n, k = threadIdx.x & 7;
+  unsigned long long tot = 0;
+  for (int E = blockIdx.x * 32 + (threadIdx.x >> 3); E < MT; E += gridDim.x * 32) {
+    const long long c = start[E + 1] - start[E];
     const int base = (E / M) * M, El = E % M;
     const int ex = El % n, ey = (El / n) % n, ez = El / (n * n);
+    const int lo = ex - NSR, hi = ex + NSR;
     long long s = 0;
-    for (int dz = -NSR; dz <= NSR; ++dz)
-      for (int dy = -NSR; dy <= NSR; ++dy)
-        for (int dx = -NSR; dx <= NSR; ++dx) {
-          const int F = base + (ex + dx + n) % n + n * ((ey + dy + n) % n + n * ((ez + dz + n) % n));
-          s += start[F + 1] - start[F];
+    if (c != 0)
+      for (int l = k; l <= 2 * NSR; l += 8) {
+        const int z = (ez + l - NSR + n) % n;
+        for (int dy = -NSR; dy <= NSR; ++dy) {
+          const int *row = start + base + n * ((ey + dy + n) % n + n * z);
+          if (lo < 0) s += (row[n] - row[lo + n]) + (row[hi + 1] - row[0]);
+          else if (hi >= n) s += (row[n] - row[lo]) + (row[hi - n + 1] - row[0]);
+          else s += row[hi + 1] - row[lo];
         }
-    atomicAdd(out, (unsigned long long)(c * s - c));
+      }
+    tot += (unsigned long long)(c * s - (k == 0 ? c : 0));
   }
+  __shared__ unsigned long long wave[4];
+  for (int o = 32; o > 0; o >>= 1) tot += __shfl_xor(tot, o, 64);
+  if ((threadIdx.x & 63) == 0) wave[threadIdx.x >> 6] = tot;
+  __syncthreads();
+  if (threadIdx.x == 0) atomicAdd(out, (wave[0] + wave[1]) + (wave[2] + wave[3]));
 }
 
 // ----------------------------------------------------------------- launchers
@@ -615,10 +636,10 @@ int launch_pair_queue(hipStream_t s, int waves, int n, int nsr, int64_t N, const
 int launch_pair_count(hipStream_t s, int nb, int n, int nsr, const int *start, unsigned long long *out) {
   const int MT = nb * n * n * n;
   switch (nsr) {
-    case 1: hipLaunchKernelGGL(k_pair_count<1>, dim3(grid_n(MT)), dim3(256), 0, s, n, MT, start, out); return 0;
-    case 2: hipLaunchKernelGGL(k_pair_count<2>, dim3(grid_n(MT)), dim3(256), 0, s, n, MT, start, out); return 0;
-    case 3: hipLaunchKernelGGL(k_pair_count<3>, dim3(grid_n(MT)), dim3(256), 0, s, n, MT, start, out); return 0;
-    case 4: hipLaunchKernelGGL(k_pair_count<4>, dim3(grid_n(MT)), dim3(256), 0, s, n, MT, start, out); return 0;
+    case 1: hipLaunchKernelGGL(k_pair_count<1>, dim3(grid_n(int64_t(MT) * 8, 512)), dim3(256), 0, s, n, MT, start, out); return 0;
+    case 2: hipLaunchKernelGGL(k_pair_count<2>, dim3(grid_n(int64_t(MT) * 8, 512)), dim3(256), 0, s, n, MT, start, out); return 0;
+    case 3: hipLaunchKernelGGL(k_pair_count<3>, dim3(grid_n(int64_t(MT) * 8, 512)), dim3(256), 0, s, n, MT, start, out); return 0;
+    case 4: hipLaunchKernelGGL(k_pair_count<4>, dim3(grid_n(int64_t(MT) * 8, 512)), dim3(256), 0, s, n, MT, start, out); return 0;
     default: return -1;
   }
 }
@@ -626,7 +647,7 @@ int launch_interp(hipStream_t s, int nb, const int *off, int p, int n, int64_t N
                   const double *sg, const double *Wel, const double *phip, const int *perm, double *phim_s,
                   double *phi_s, double *Phi) {
 #define CALL(PO)                                                                                                 \
-  hipLaunchKernelGGL(k_interp<PO>, dim3(grid_n(N)), dim3(256), 0, s, n, N, nb, off, inv_h, bas, sg, Wel, phip, perm, \
+  hipLaunchKernelGGL(k_interp<PO>, dim3(grid_n((PO <= 3 ? 4 : 8) * N, 65536)), dim3(256), 0, s, n, N, nb, off, inv_h, bas, sg, Wel, phip, perm, \
                      phim_s, phi_s, Phi)
   switch (p) {
     case 3: CALL(3); return 0;
