@@ -101,7 +101,9 @@ enum ApplyMode : int {
   kChebZ2 = 5,     // as kCheb with x = s0 D^-1 f (built from f on the fly) and x_prev = 0
   kChebZ3 = 6,     // as kCheb with x_prev = s0 D^-1 f
   kResidualRestrict = 7,  // f - K x restricted to the next level, not stored (launch_march_restrict)
-  kChebDot = 8     // as kCheb, and block partials of x_new . f
+  kChebDot = 8,    // as kCheb, and block partials of x_new . f
+  // 9: k_march.hip's own
+  kResidualNorm = 10  // block partials of r . r, r = f - K x (not stored), and of f . f (the latter in out); orders 3 to 6
 };
 
 }  // namespace fep3m

@@ -12,56 +12,266 @@
 // solve is  x^ = (W (x) W (x) W) diag(1 / (lam_x + lam_y + lam_z)) (W (x) W (x) W)^H b^
 // (the constant mode, all three null modes at f = 0, dropped: int phi = 0).
 //
-// Data path per solve: gather the mesh vector into element-major complex
-// channels [E][kz][ky][kx] (two real systems as the real and imaginary
-// parts of one complex system: the operator is real), three FFT passes over
-// the element lattice, the per-frequency block solve, three inverse passes,
-// scatter back (real part: first system, imaginary part: second).
+// Data path per solve (two real systems as the real and imaginary parts of
+// one complex system: the operator is real): an FFT along x that reads the
+// mesh vectors and writes element-major complex channels [E][kz][ky][kx], an
+// FFT along y, one kernel for the FFT along z, the blocks' solve and the way
+// back along z, then y and x, the last into the mesh vectors (real part:
+// first system, imaginary part: second).
+#include <algorithm>
+#include <type_traits>
+
 #include "kernels.hpp"
 
 namespace fep3m {
 namespace {
 
-// Mesh vectors of systems 2c and 2c + 1 -> complex system c, element-major.
-template <int PO>
-__global__ __launch_bounds__(256) void k_fs_gather(int n, int nsys, const double *__restrict__ v,
-                                                   double2 *__restrict__ Z) {
-  constexpr int NCH = PO * PO * PO;
-  const int P = PO * n;
-  const size_t per = size_t(P) * P * P;
-  const int ncs = (nsys + 1) / 2;
-  for (size_t t = size_t(blockIdx.x) * blockDim.x + threadIdx.x; t < per * ncs; t += size_t(gridDim.x) * blockDim.x) {
-    const int cs = int(t / per);
-    const size_t g = t % per;
-    const int gx = int(g % P), gy = int((g / P) % P), gz = int(g / (size_t(P) * P));
-    const int ex = gx / PO, ey = gy / PO, ez = gz / PO;
-    const int k = ((gz - PO * ez) * PO + (gy - PO * ey)) * PO + (gx - PO * ex);
-    const double re = v[size_t(2 * cs) * per + g];
-    const double im = (2 * cs + 1 < nsys) ? v[size_t(2 * cs + 1) * per + g] : 0.0;
-    Z[(size_t(cs) * n * n * n + (size_t(ez) * n + ey) * n + ex) * NCH + k] = make_double2(re, im);
+__device__ __forceinline__ double2 zadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
+__device__ __forceinline__ double2 zsub(double2 a, double2 b) { return make_double2(a.x - b.x, a.y - b.y); }
+__device__ __forceinline__ double2 zmul(double2 a, double2 b) {
+  return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+}
+
+// v <- its DFT over R = 1, 2, 4 or 8 values, in natural order; INV: the
+// conjugate factors.
+template <int R, bool INV>
+__device__ __forceinline__ void dft(double2 (&v)[R]) {
+  if constexpr (R == 2) {
+    const double2 a = v[0];
+    v[0] = zadd(a, v[1]);
+    v[1] = zsub(a, v[1]);
+  } else if constexpr (R > 2) {
+    constexpr int H = R / 2;
+    constexpr double S = 0.70710678118654752440;
+    double2 e[H], o[H];
+#pragma unroll
+    for (int k = 0; k < H; ++k) {
+      e[k] = v[2 * k];
+      o[k] = v[2 * k + 1];
+    }
+    dft<H, INV>(e);
+    dft<H, INV>(o);
+#pragma unroll
+    for (int k = 0; k < H; ++k) {   // o[k] times exp(-+ 2 pi i k / R)
+      double2 t = o[k];
+      if (4 * k == R) t = INV ? make_double2(-t.y, t.x) : make_double2(t.y, -t.x);
+      else if (8 * k == R) t = INV ? make_double2(S * (t.x - t.y), S * (t.x + t.y)) : make_double2(S * (t.x + t.y), S * (t.y - t.x));
+      else if (8 * k == 3 * R) t = INV ? make_double2(-S * (t.x + t.y), S * (t.x - t.y)) : make_double2(S * (t.y - t.x), -S * (t.x + t.y));
+      v[k] = zadd(e[k], t);
+      v[k + H] = zsub(e[k], t);
+    }
   }
 }
 
-template <int PO>
-__global__ __launch_bounds__(256) void k_fs_scatter(int n, int nsys, const double2 *__restrict__ Z,
-                                                    double *__restrict__ v) {
-  constexpr int NCH = PO * PO * PO;
-  const int P = PO * n;
-  const size_t per = size_t(P) * P * P;
-  const int ncs = (nsys + 1) / 2;
-  for (size_t t = size_t(blockIdx.x) * blockDim.x + threadIdx.x; t < per * ncs; t += size_t(gridDim.x) * blockDim.x) {
-    const int cs = int(t / per);
-    const size_t g = t % per;
-    const int gx = int(g % P), gy = int((g / P) % P), gz = int(g / (size_t(P) * P));
-    const int ex = gx / PO, ey = gy / PO, ez = gz / PO;
-    const int k = ((gz - PO * ez) * PO + (gy - PO * ey)) * PO + (gx - PO * ex);
-    const double2 z = Z[(size_t(cs) * n * n * n + (size_t(ez) * n + ey) * n + ex) * NCH + k];
-    v[size_t(2 * cs) * per + g] = z.x;
-    if (2 * cs + 1 < nsys) v[size_t(2 * cs + 1) * per + g] = z.y;
+// The z direction of the solve: for each (fx, fy) the n p^3 values along z
+// stand in LDS while they are transformed (n = A B: z = g + A m to f = k1 +
+// B k2, slot k1 A + k2), multiplied by W^H along x, y and z, divided by the
+// eigenvalue sums (times scale, the inverse transforms' 1 / n^3), multiplied
+// back and transformed back, so that they cross memory once each way.
+// W[f][k][i]: component k of mode i of frequency f; lam[f][i].
+//
+// Bound by float64 arithmetic (the six 1-D products, 9600 complex dots of p
+// per 64 x 125 values) and LDS, at one block of 16 waves per compute unit for
+// p = 5, n = 64 (128 KB); the next column's values are loaded into registers
+// meanwhile.  A wave takes whole slots, p^2 lines at a time, so the products'
+// steps need no block barrier, and W is uniform (x, y) or read by broadcast
+// (z).  Separate z passes and a solve of one block per frequency triple took
+// 235 + 551 + 223 us at 64^3, p = 5 (three trips through memory); this 516.
+template <int PO, int LOGN>
+struct ZSolve {
+  static constexpr int N = 1 << LOGN, NCH = PO * PO * PO, P2 = PO * PO;
+  static constexpr int A = LOGN >= 6 ? 8 : LOGN >= 4 ? 4 : 1, B = N / A;
+  static constexpr int NT = A * NCH <= 256 ? 256 : (A * NCH + 63) / 64 * 64;
+  static constexpr size_t LDS = (size_t(N) * NCH + N) * sizeof(double2);
+  static constexpr bool OK = NT <= 1024 && LDS + 64 <= 160 * 1024;
+};
+
+// orders the LDS accesses of one wave's lanes
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+typedef const f64x2 __attribute__((address_space(4))) *CPtr;
+typedef const f64x2 __attribute__((address_space(1))) *GPtr;
+
+// v <- conj(W)^T v (TRANS, into modes) or W v for one line of PO values.  The
+// pointer is made opaque at each row, so that one row of W is held at a time
+// (in scalar registers where it is uniform): all 25 at once spilled.
+template <int PO, bool TRANS, class Ptr>
+__device__ __forceinline__ void mode_line(Ptr w, double2 (&v)[PO]) {
+  double2 r[PO];
+#pragma unroll
+  for (int i = 0; i < PO; ++i) r[i] = make_double2(0.0, 0.0);
+#pragma unroll
+  for (int k = 0; k < PO; ++k) {
+    double &last = TRANS ? r[PO - 1].y : r[k > 0 ? k - 1 : 0].y;   // of the row before
+    if constexpr (std::is_same_v<Ptr, CPtr>) asm volatile("" : "+s"(w), "+v"(last));
+    else asm volatile("" : "+v"(w), "+v"(last));
+#pragma unroll
+    for (int i = 0; i < PO; ++i) {
+      const f64x2 a = w[k * PO + i];
+      if (TRANS) {   // out i += conj(W[k][i]) in k
+        r[i].x = fma(a.y, v[k].y, fma(a.x, v[k].x, r[i].x));
+        r[i].y = fma(-a.y, v[k].x, fma(a.x, v[k].y, r[i].y));
+      } else {       // out k += W[k][i] in i
+        r[k].x = fma(-a.y, v[i].y, fma(a.x, v[i].x, r[k].x));
+        r[k].y = fma(a.y, v[i].x, fma(a.x, v[i].y, r[k].y));
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < PO; ++i) v[i] = r[i];
+}
+
+template <int PO, int LOGN>
+__global__ __launch_bounds__((ZSolve<PO, LOGN>::NT), 4) void k_fs_zsolve(int items, const double2 *__restrict__ W,
+                                                                      const double *__restrict__ lam,
+                                                                      const double2 *__restrict__ tw, double2 *Z,
+                                                                      double scale) {
+  using C = ZSolve<PO, LOGN>;
+  constexpr int N = C::N, NCH = C::NCH, P2 = C::P2, A = C::A, B = C::B, NT = C::NT;
+  constexpr int SPW = 64 / P2;   // slots a wave takes at a time
+  extern __shared__ double2 zlds[];
+  double2 *buf = zlds, *tws = zlds + N * NCH;
+  constexpr size_t SZ = size_t(N) * N * NCH;
+  // opaque, so that what follows from it is formed where it is needed and not
+  // kept in registers over the whole loop (28 spilled)
+  auto fresh = [](int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+  };
+  auto base = [](int it) { return size_t(it / (N * N)) * N * SZ + size_t(it % (N * N)) * NCH; };
+  if (threadIdx.x < N) tws[threadIdx.x] = tw[threadIdx.x];
+#pragma unroll 1
+  for (int it = blockIdx.x; it < items; it += gridDim.x) {
+    __syncthreads();   // the slots of the item before are read
+    int tid = fresh(threadIdx.x);
+    if (tid < A * NCH) {   // thread (g, c)
+      const int g1 = tid / NCH, c1 = tid - g1 * NCH;
+      const double2 *src = Z + base(it) + (unsigned(g1) * unsigned(SZ) + c1);
+      double2 v[B];
+#pragma unroll
+      for (int k = 0; k < B; ++k) v[k] = src[size_t(A * k) * SZ];
+      dft<B, false>(v);
+#pragma unroll
+      for (int k = 0; k < B; ++k) buf[(k * A + g1) * NCH + c1] = A == 1 ? v[k] : zmul(v[k], tws[g1 * k]);
+    }
+    __syncthreads();
+    if constexpr (A > 1) {
+#pragma unroll 1
+      for (int t = fresh(threadIdx.x); t < B * NCH; t += NT) {
+        const int k1 = t / NCH;
+        double2 *s = buf + k1 * A * NCH + (t - k1 * NCH);
+        double2 v[A];
+#pragma unroll
+        for (int g = 0; g < A; ++g) v[g] = s[g * NCH];
+        dft<A, false>(v);
+#pragma unroll
+        for (int g = 0; g < A; ++g) s[g * NCH] = v[g];
+      }
+      __syncthreads();
+    }
+    {
+      const int fx = it % N, fy = it / N % N;
+      const CPtr wx = (CPtr)(W + fx * P2), wy = (CPtr)(W + fy * P2);
+      tid = fresh(threadIdx.x);
+      const int lane = tid & 63, wave = tid >> 6;
+      const int sl = lane / P2, ln = lane - sl * P2, la = ln % PO, lb = ln / PO;
+#pragma unroll 1
+      for (int s0 = wave * SPW; s0 < N; s0 += NT / 64 * SPW) {   // the same trip count for a wave's lanes
+        const int slot = s0 + sl;
+        const bool on = sl < SPW && slot < N;
+        double2 *q = buf + (on ? slot : 0) * NCH;
+        const int fz = A == 1 ? slot : slot / A + B * (slot % A);
+        double2 v[PO];
+        // lines along x: (ky, kz) = (la, lb); y: (kx, kz); z: (kx, ky)
+        auto load = [&](int o, int stride) {
+#pragma unroll
+          for (int k = 0; k < PO; ++k) v[k] = q[o + k * stride];
+        };
+        auto store = [&](int o, int stride) {
+          if (on) {
+#pragma unroll
+            for (int k = 0; k < PO; ++k) q[o + k * stride] = v[k];
+          }
+          wave_sync();
+        };
+        load(on ? ln * PO : 0, 1);
+        mode_line<PO, true>(wx, v);
+        store(ln * PO, 1);
+        load(on ? lb * P2 + la : 0, PO);
+        mode_line<PO, true>(wy, v);
+        store(lb * P2 + la, PO);
+        load(on ? ln : 0, P2);
+        {
+          const GPtr wz = (GPtr)(W + (on ? fz : 0) * P2);
+          mode_line<PO, true>(wz, v);
+          const double lxy = lam[fx * PO + la % PO] + lam[fy * PO + (lb < PO ? lb : 0)];
+#pragma unroll
+          for (int k = 0; k < PO; ++k) {
+            const double den = lxy + lam[(on ? fz : 0) * PO + k];
+            const double r = den == 0.0 ? 0.0 : scale / den;
+            v[k].x *= r;
+            v[k].y *= r;
+            if (k + 1 < PO) asm volatile("" : "+v"(v[k].x), "+v"(v[k + 1].x));   // one division at a time
+          }
+          mode_line<PO, false>(wz, v);
+        }
+        store(ln, P2);
+        load(on ? lb * P2 + la : 0, PO);
+        mode_line<PO, false>(wy, v);
+        store(lb * P2 + la, PO);
+        load(on ? ln * PO : 0, 1);
+        mode_line<PO, false>(wx, v);
+        store(ln * PO, 1);
+      }
+    }
+    __syncthreads();
+    if constexpr (A > 1) {
+#pragma unroll 1
+      for (int t = fresh(threadIdx.x); t < B * NCH; t += NT) {
+        const int k1 = t / NCH;
+        double2 *s = buf + k1 * A * NCH + (t - k1 * NCH);
+        double2 v[A];
+#pragma unroll
+        for (int g = 0; g < A; ++g) v[g] = s[g * NCH];
+        dft<A, true>(v);
+#pragma unroll
+        for (int g = 0; g < A; ++g) {
+          const double2 w = tws[g * k1];
+          s[g * NCH] = zmul(v[g], make_double2(w.x, -w.y));
+        }
+      }
+      __syncthreads();
+    }
+    tid = fresh(threadIdx.x);
+    if (tid < A * NCH) {
+      const int g1 = tid / NCH, c1 = tid - g1 * NCH;
+      double2 v[B];
+#pragma unroll
+      for (int k = 0; k < B; ++k) v[k] = buf[(k * A + g1) * NCH + c1];
+      dft<B, true>(v);
+      double2 *dst = Z + base(it) + (unsigned(g1) * unsigned(SZ) + c1);
+#pragma unroll
+      for (int k = 0; k < B; ++k) dst[size_t(A * k) * SZ] = v[k];
+    }
   }
 }
 
-// One frequency triple per block: the p^3 values of complex system cs at
+template <int PO, int LOGN>
+void zsolve(hipStream_t s, int ncs, const double2 *W, const double *lam, const double2 *tw, double2 *Z, double scale) {
+  using C = ZSolve<PO, LOGN>;
+  const int items = ncs << (2 * LOGN);
+  // as many blocks as stay resident (LDS; waves of at most 128 registers)
+  const int per_cu = int(std::min<size_t>(160 * 1024 / (C::LDS + 64), size_t(std::max(1, 1024 / C::NT))));
+  hipLaunchKernelGGL((k_fs_zsolve<PO, LOGN>), dim3(std::min(items, 256 * per_cu)), dim3(C::NT), C::LDS, s, items, W, lam,
+                     tw, Z, scale);
+}
+
+// The same products alone, where the z direction does not fit LDS (p = 6, n =
+// 64).  One frequency triple per block: the p^3 values of complex system cs at
 // (fx, fy, fz), transformed by W^H along x, y, z, divided by the eigenvalue
 // sums (times `scale`, the inverse transform's 1 / n^3), transformed back.
 // W[f][k][i]: component k of mode i of frequency f; lam[f][i].
@@ -274,15 +484,28 @@ inline int grid_of(size_t count) {
 template <int PO>
 int fs_solve_impl(hipStream_t s, int nsys, int n, const double *rhs, double *out, double2 *Z, const double2 *tw,
                   const double2 *W, const double *lam) {
-  const size_t P = size_t(PO) * n, per = P * P * P;
   const int ncs = (nsys + 1) / 2;
   const size_t M = size_t(n) * n * n;
-  hipLaunchKernelGGL(k_fs_gather<PO>, dim3(grid_of(per * ncs)), dim3(256), 0, s, n, nsys, rhs, Z);
-  if (launch_fft3_nodes(s, ncs, n, PO * PO * PO, Z, tw, false) != 0) return -1;
-  hipLaunchKernelGGL(k_fs_solve<PO>, dim3(unsigned(M * ncs)), dim3(256), 0, s, n, W, lam, Z, 1.0 / double(M));
-  if (launch_fft3_nodes(s, ncs, n, PO * PO * PO, Z, tw, true) != 0) return -1;
-  hipLaunchKernelGGL(k_fs_scatter<PO>, dim3(grid_of(per * ncs)), dim3(256), 0, s, n, nsys, Z, out);
-  return 0;
+  const double scale = 1.0 / double(M);
+  constexpr int NCH = PO * PO * PO;
+  if (launch_fft_nodes_from_mesh(s, nsys, n, PO, rhs, Z, tw) != 0) return -1;
+  if (launch_fft_nodes(s, ncs, n, NCH, 1, Z, tw, false) != 0) return -1;
+  bool done = true;
+  switch (n) {
+    case 8: zsolve<PO, 3>(s, ncs, W, lam, tw, Z, scale); break;
+    case 16: zsolve<PO, 4>(s, ncs, W, lam, tw, Z, scale); break;
+    case 32: zsolve<PO, 5>(s, ncs, W, lam, tw, Z, scale); break;
+    default:
+      if constexpr (ZSolve<PO, 6>::OK) zsolve<PO, 6>(s, ncs, W, lam, tw, Z, scale);
+      else done = false;
+  }
+  if (!done) {
+    launch_fft_nodes(s, ncs, n, NCH, 2, Z, tw, false);
+    hipLaunchKernelGGL(k_fs_solve<PO>, dim3(unsigned(M * ncs)), dim3(256), 0, s, n, W, lam, Z, scale);
+    launch_fft_nodes(s, ncs, n, NCH, 2, Z, tw, true);
+  }
+  launch_fft_nodes(s, ncs, n, NCH, 1, Z, tw, true);
+  return launch_fft_nodes_to_mesh(s, nsys, n, PO, Z, out, tw);
 }
 
 }  // namespace

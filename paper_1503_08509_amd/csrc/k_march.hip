@@ -195,15 +195,17 @@ __global__ __launch_bounds__(NT, WPS) void k_apply_march(MarchOp<T, PO> op, Marc
   constexpr bool zstart = MODE == kChebZ2, need_d = MODE == kCheb || MODE == kChebDot;
   constexpr bool cheb = need_d || MODE == kChebFirst;
   constexpr bool rr = MODE == kResidualRestrict;
-  constexpr bool need_f = MODE == kResidual || rr || cheb || zstart || MODE == kChebZ3;
+  constexpr bool norm = MODE == kResidualNorm;
+  constexpr bool need_f = MODE == kResidual || norm || rr || cheb || zstart || MODE == kChebZ3;
   constexpr bool need_x = cheb || MODE == kChebZ3 || MODE == kApplyDot;
-  constexpr bool need_id = MODE != kApply && MODE != kApplyDot && MODE != kResidual && !rr;
+  constexpr bool need_id = MODE != kApply && MODE != kApplyDot && MODE != kResidual && !norm && !rr;
   __shared__ T AB[2 * PO * S::SA];
   __shared__ T Xo[need_x || rr ? S::OWN : 1];   // x (rr: the residual) on the owned nodes
   __shared__ T invd[PO * PO * PO];
   // dot modes: each thread's sum, kept in LDS between steps
-  constexpr bool dot = MODE == kApplyDot || MODE == kChebDot;
+  constexpr bool dot = MODE == kApplyDot || MODE == kChebDot || norm;
   __shared__ double sum[dot ? NT : 1];
+  __shared__ double sum2[norm ? NT : 1];
   const int P = op.P, n = op.n;
   const size_t P2 = size_t(P) * P;
   const int ntx = (n + TX - 1) / TX, nty = (n + TY - 1) / TY, nz = (n + ze - 1) / ze;
@@ -283,6 +285,7 @@ __global__ __launch_bounds__(NT, WPS) void k_apply_march(MarchOp<T, PO> op, Marc
     }
   }
   if (dot) sum[tid] = 0.0;
+  if (norm) sum2[tid] = 0.0;
   // pass z of element e: its rows from the PO + 1 input planes; the upper
   // vertex row is carried to the next element
   auto pass_z = [&]() {
@@ -494,7 +497,7 @@ __global__ __launch_bounds__(NT, WPS) void k_apply_march(MarchOp<T, PO> op, Marc
       continue;
     }
     T res[NIT];
-    double acc = dot ? sum[tid] : 0.0;
+    double acc = dot ? sum[tid] : 0.0, acc2 = norm ? sum2[tid] : 0.0;
 #pragma unroll
     for (int r = 0; r < NIT; ++r) {
       const T y = AB[eidx[r] & 0xffff], id = need_id ? invd[(eidx[r] >> 16) & 0x7fff] : T(0);
@@ -503,20 +506,27 @@ __global__ __launch_bounds__(NT, WPS) void k_apply_march(MarchOp<T, PO> op, Marc
       const T rr = (pf_f[r] - y) * id;
       T v;
       if (MODE == kApply || MODE == kApplyDot) v = y;
-      else if (MODE == kResidual) v = pf_f[r] - y;
+      else if (MODE == kResidual || norm) v = pf_f[r] - y;
       else if (need_d) v = xv + c1 * (xv - pf_d[r]) + c2 * rr;
       else if (cheb || zstart) v = xv + c1 * xv + c2 * rr;
       else if (MODE == kChebZ3) v = xv + c1 * (xv - s0 * id * pf_f[r]) + c2 * rr;
       else v = -rr;
       if (MODE == kApplyDot && int(eidx[r]) < 0) acc += double(xv) * double(y);
       if (MODE == kChebDot && int(eidx[r]) < 0) acc += double(v) * double(pf_f[r]);
+      if (norm && int(eidx[r]) < 0) {
+        acc += double(v) * double(v);
+        acc2 += double(pf_f[r]) * double(pf_f[r]);
+      }
       res[r] = v;
     }
     if (dot) sum[tid] = acc;
-    T *const dst = out + tb;
+    if (norm) sum2[tid] = acc2;
+    if (!norm) {
+      T *const dst = out + tb;
 #pragma unroll
-    for (int r = 0; r < NIT; ++r)
-      if (int(eidx[r]) < 0) at(dst, eoff[r]) = res[r];
+      for (int r = 0; r < NIT; ++r)
+        if (int(eidx[r]) < 0) at(dst, eoff[r]) = res[r];
+    }
     __syncthreads();   // the next z pass overwrites what the epilogue read
   }
   if (dot) {
@@ -524,6 +534,13 @@ __global__ __launch_bounds__(NT, WPS) void k_apply_march(MarchOp<T, PO> op, Marc
     __syncthreads();
     t = block_sum_waves(t, sum);
     if (tid == 0) partial[blk] = t;   // blk is system-major
+    if (norm) {
+      __syncthreads();
+      double t2 = sum2[tid];
+      __syncthreads();
+      t2 = block_sum_waves(t2, sum2);
+      if (tid == 0) out[blk] = T(t2);
+    }
   }
 }
 
@@ -636,6 +653,13 @@ int march_impl(hipStream_t s, int nsys, const MarchPlan &pl, const LevelOpT<T> &
     FEP3M_MARCH(kChebZ2);
     FEP3M_MARCH(kChebZ3);
     FEP3M_MARCH(kChebDot);
+    case kResidualNorm:
+      if constexpr (sizeof(T) == 8) {
+        switch (mode) { FEP3M_MARCH(kResidualNorm); }
+        break;
+      } else {
+        return -1;
+      }
     case kResidualRestrict:
       if constexpr (PO > 3 && sizeof(T) == 8) {
         switch (mode) { FEP3M_MARCH(kResidualRestrict); }

@@ -240,8 +240,12 @@ int launch_fs_solve(hipStream_t s, int nsys, int n, int p, const double *rhs, do
 // V^T, else V.
 void launch_axis_transform(hipStream_t s, int P, int axis, int nsys, const double *V, bool to_modes, const double *in,
                            double *out);
-// in-place 3-D FFT of [nb][z][y][x][nch] complex arrays, nch = p^3 (k_fft.hip)
-int launch_fft3_nodes(hipStream_t s, int nb, int n, int nch, double2 *z, const double2 *tw, bool inverse);
+// FFT along one axis of [nb][z][y][x][nch] complex arrays in place, nch = p^3
+// (k_fft.hip); along x from nsys real mesh vectors, two to a complex array, and
+// back into them
+int launch_fft_nodes(hipStream_t s, int nb, int n, int nch, int axis, double2 *z, const double2 *tw, bool inverse);
+int launch_fft_nodes_from_mesh(hipStream_t s, int nsys, int n, int p, const double *v, double2 *z, const double2 *tw);
+int launch_fft_nodes_to_mesh(hipStream_t s, int nsys, int n, int p, double2 *z, double *v, const double2 *tw);
 
 // mesh (k_mesh.hip).  nb configurations; per-configuration reductions
 // write nb * K block partials (K = seg_blocks(nb, per) unless a launcher
