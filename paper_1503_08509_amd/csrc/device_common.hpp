@@ -83,6 +83,15 @@ __device__ __forceinline__ int xcd_linear(int b, int total) {
   return (b & 7) * (total >> 3) + (b >> 3);
 }
 
+// 1 / sqrt(x) for a positive normal x: the hardware estimate refined by one
+// Newton-Raphson step y <- y (3 - x y^2) / 2, written as y + y e / 2 with
+// e = 1 - x y^2 (one step squares the estimate's relative error).
+__device__ __forceinline__ double rsqrt_pos(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(0.5 * y, e, y);
+}
+
 // Device arrays (nb values each) of the per-configuration PCG scalars.
 struct PcgScalars {
   double *bn2, *rz, *rzn, *pq, *rr, *zq, *alpha, *beta, *act, *rel;

@@ -5,7 +5,7 @@
 // the box are nb consecutive (p n + 1)^3 blocks [z][y][x], global node
 // g = p e + k along each axis, no wrap.
 //
-//   boundary values   one thread per (configuration, face node): the node's
+//   boundary values   one block per (configuration, face element): the node's
 //                     element e = min(g / p, n - 1) per axis, its local node
 //                     m; Phi_sr = sum over the charges of e's near block (cut
 //                     at the faces) of Q_j / |x_B - x_j| minus the block's
@@ -35,53 +35,87 @@ namespace {
 
 __device__ __forceinline__ int node_elem(int g, int PO, int n) { return min(g / PO, n - 1); }
 
+// One block per (configuration, face, element of the face): its PO^2 nodes
+// (one row more at the last element; nodes on the faces of a lower axis are
+// those faces') see one near block, whose charges are staged in LDS and split
+// over the 256 / nodes groups of threads.  Bound by the arithmetic of the
+// pairs and the LDS reads of their charges.  One thread per node left 2400
+// waves with a serial chain of loads each: 287 us at 32^3 elements with
+// 100000 charges (488 with eight lanes per node); 73 us so.
 template <int PO>
 __global__ __launch_bounds__(256) void k_box_bvals(int n, int nsr, int nb, int64_t N, BoxNodes nodes,
                                                    const int *__restrict__ start, const double *__restrict__ sg,
                                                    const double *__restrict__ sQ, const double *__restrict__ Wneg,
                                                    double *__restrict__ phiB) {
-  constexpr int Q1 = PO + 1, NM = Q1 * Q1 * Q1;
-  const int P = PO * n + 1;
+  constexpr int Q1 = PO + 1, NM = Q1 * Q1 * Q1, CAP = 512, RM = 49;   // rows of the near block (n_sr <= 3)
+  __shared__ double4 ch[CAP];
+  __shared__ double red[256], xn[8];
+  __shared__ int rb[RM], pre[RM + 1];
+  const int P = PO * n + 1, tid = threadIdx.x;
   const size_t P2 = size_t(P) * P, per = P2 * P, M = size_t(n) * n * n;
-  const size_t total = size_t(nb) * 6 * P2;
-  for (size_t t = size_t(blockIdx.x) * blockDim.x + threadIdx.x; t < total; t += size_t(gridDim.x) * blockDim.x) {
-    const int cfg = int(t / (6 * P2));
-    const size_t r = t % (6 * P2);
-    const int face = int(r / P2), a = int((r % P2) % P), b = int((r % P2) / P);
-    const int ax = face >> 1, side = face & 1;
-    int g[3];
-    g[ax] = side ? P - 1 : 0;
-    g[ax == 0 ? 1 : 0] = a;
-    g[ax == 2 ? 1 : 2] = b;
-    int e[3], k[3];
-    double xb[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      e[c] = node_elem(g[c], PO, n);
-      k[c] = g[c] - PO * e[c];
-      xb[c] = e[c] + 0.5 + nodes.x[k[c]];
-    }
-    const size_t cbase = size_t(cfg) * M;
-    double pairs = 0.0;
-    for (int dz = -nsr; dz <= nsr; ++dz) {
-      const int sz = e[2] + dz;
-      if (sz < 0 || sz >= n) continue;
-      for (int dy = -nsr; dy <= nsr; ++dy) {
-        const int sy = e[1] + dy;
-        if (sy < 0 || sy >= n) continue;
-        const int sx0 = max(e[0] - nsr, 0), sx1 = min(e[0] + nsr, n - 1);
-        const size_t row = cbase + size_t(n) * (sy + size_t(n) * sz);
-        // the elements sx0 .. sx1 of one row are consecutive in the sorted order
-        for (int s = start[row + sx0]; s < start[row + sx1 + 1]; ++s) {
-          const double dx = sg[s] - xb[0], dyv = sg[N + s] - xb[1], dzv = sg[2 * N + s] - xb[2];
-          pairs += sQ[s] / sqrt(dx * dx + dyv * dyv + dzv * dzv);
-        }
+  const int n2 = n * n, cfg = blockIdx.x / (6 * n2), f = blockIdx.x % (6 * n2);
+  const int face = f / n2, ax = face >> 1, side = face & 1;
+  const int t0 = ax == 0 ? 1 : 0, t1 = ax == 2 ? 1 : 2;   // tangential axes
+  int e[3];
+  e[ax] = side ? n - 1 : 0;
+  e[t0] = f % n;
+  e[t1] = f / n % n;
+  const size_t cbase = size_t(cfg) * M;
+  const int y0 = max(e[1] - nsr, 0), ny = min(e[1] + nsr, n - 1) - y0 + 1;
+  const int z0 = max(e[2] - nsr, 0), nz = min(e[2] + nsr, n - 1) - z0 + 1;
+  const int x0 = max(e[0] - nsr, 0), x1 = min(e[0] + nsr, n - 1), rows = ny * nz;
+  if (tid < 8) xn[tid] = nodes.x[tid];
+  if (tid < rows) {   // the elements x0 .. x1 of one row are consecutive in the sorted order
+    const size_t row = cbase + size_t(n) * (y0 + tid % ny + size_t(n) * (z0 + tid / ny));
+    rb[tid] = start[row + x0];
+    pre[tid + 1] = start[row + x1 + 1] - rb[tid];
+  }
+  __syncthreads();
+  if (tid == 0) {
+    pre[0] = 0;
+    for (int r = 0; r < rows; ++r) pre[r + 1] += pre[r];
+  }
+  __syncthreads();
+  const int total = pre[rows];
+  // this thread's node and share of the charges
+  const int u0 = t0 < ax && e[t0] == 0 ? 1 : 0, v0 = t1 < ax && e[t1] == 0 ? 1 : 0;
+  const int cu = (e[t0] == n - 1 ? (t0 < ax ? PO : PO + 1) : PO) - u0, cv = (e[t1] == n - 1 ? (t1 < ax ? PO : PO + 1) : PO) - v0;
+  const int cnt = cu * cv, G = 256 / cnt, node = tid % cnt, grp = tid / cnt;
+  int k[3];
+  k[ax] = side ? PO : 0;
+  k[t0] = u0 + node % cu;
+  k[t1] = v0 + node / cu;
+  const double xb0 = e[0] + 0.5 + xn[k[0]], xb1 = e[1] + 0.5 + xn[k[1]], xb2 = e[2] + 0.5 + xn[k[2]];
+  double pairs = 0.0;
+  for (int c0 = 0; c0 < total; c0 += CAP) {
+    if (c0 > 0) __syncthreads();   // the chunk before is read
+    for (int r = tid >> 6; r < rows; r += 4) {
+      const int lo = max(pre[r], c0), hi = min(pre[r + 1], c0 + CAP);
+      for (int i = lo + (tid & 63); i < hi; i += 64) {
+        const int s = rb[r] + i - pre[r];
+        ch[i - c0] = make_double4(sg[s], sg[N + s], sg[2 * N + s], sQ[s]);
       }
     }
+    __syncthreads();
+    if (grp < G) {
+      const int m = min(CAP, total - c0);
+      for (int i = grp; i < m; i += G) {
+        const double4 c = ch[i];
+        const double dx = c.x - xb0, dy = c.y - xb1, dz = c.z - xb2;
+        pairs = fma(c.w, rsqrt_pos(fma(dx, dx, fma(dy, dy, dz * dz))), pairs);
+      }
+    }
+  }
+  red[tid] = pairs;
+  __syncthreads();
+  if (tid < cnt) {
+    double s = red[tid];
+    for (int g = 1; g < G; ++g) s += red[g * cnt + tid];
     const size_t E = cbase + e[0] + size_t(n) * (e[1] + size_t(n) * e[2]);
     const int m = k[0] + Q1 * (k[1] + Q1 * k[2]);
     // Phi_sr = pairs - Psi = pairs + Wneg; the mesh takes -Phi_sr
-    phiB[size_t(cfg) * per + (size_t(g[2]) * P + g[1]) * P + g[0]] = -(pairs + Wneg[E * NM + m]);
+    phiB[size_t(cfg) * per + (size_t(PO * e[2] + k[2]) * P + PO * e[1] + k[1]) * P + PO * e[0] + k[0]] =
+        -(s + Wneg[E * NM + m]);
   }
 }
 
@@ -300,13 +334,22 @@ __device__ __forceinline__ bool far_from_faces(const int (&Ec)[3], int n, int ns
 // boundary nodes whose element's near block holds it (each visited once, as
 // in for_near_boundary); F += s2 Q bp / 2 and dU/dQ -= inv_h bq / 2 (physical
 // units), in caller order.  One wave per charge: the lanes split the nodes
-// of each face's range and the wave sums them.
+// of each face's range and the wave sums them.  Bound by the arithmetic of
+// the pairs: a lane steps its (row, column) without division, takes the
+// node coordinates from the wave's table and sums the face's two tangential
+// moments and the plain one (338 us at 32^3 elements with 100000 charges
+// when it worked each node out from its index; 134 us so).
 template <int PO>
 __global__ __launch_bounds__(256) void k_box_charge_bnd(int n, int nsr, int nb, int64_t N, const int *__restrict__ off,
                                                         double inv_h, BoxNodes nodes, const double *__restrict__ sg,
                                                         const double *__restrict__ sQ, const double *__restrict__ mu,
                                                         const int *__restrict__ perm, double *__restrict__ F,
                                                         double *__restrict__ dUdQ) {
+  constexpr int LM = PO * 7 + 1;   // nodes of seven elements (n_sr <= 3)
+  __shared__ double pos[4][3][LM], xn[8];
+  if (threadIdx.x < 8) xn[threadIdx.x] = nodes.x[threadIdx.x];
+  __syncthreads();
+  double(&ps)[3][LM] = pos[threadIdx.x >> 6];
   const int P = PO * n + 1;
   const size_t per = size_t(P) * P * P;
   const int lane = threadIdx.x & 63;
@@ -325,38 +368,57 @@ __global__ __launch_bounds__(256) void k_box_charge_bnd(int n, int nsr, int nb, 
       lo[c] = PO * el;
       hi[c] = eh == n - 1 ? P - 1 : PO * eh + PO - 1;
     }
-    double bx = 0.0, by = 0.0, bz = 0.0, bq = 0.0;
-    for (int face = 0; face < 6; ++face) {
-      const int ax = face >> 1, side = face & 1;
-      if (side == 0 ? Ec[ax] > nsr : (n - 1 - Ec[ax]) > nsr) continue;
-      int a0[3], len[3];
+    // node coordinates along each axis from lo (the wave's own table: its
+    // accesses stay in order)
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    if (lane < LM) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
-        int u0 = lo[c], u1 = hi[c];
-        if (c < ax) {   // nodes on the faces of a lower axis were visited there
-          u0 = max(u0, 1);
-          u1 = min(u1, P - 2);
-        }
-        if (c == ax) u0 = u1 = side ? P - 1 : 0;
-        a0[c] = u0;
-        len[c] = u1 - u0 + 1;
+        const int g = min(lo[c] + lane, P - 1), e = node_elem(g, PO, n);
+        ps[c][lane] = e + 0.5 + xn[g - PO * e];
       }
-      const int count = len[0] * len[1] * len[2];
-      for (int idx = lane; idx < count; idx += 64) {
-        const int g[3] = {a0[0] + idx % len[0], a0[1] + (idx / len[0]) % len[1], a0[2] + idx / (len[0] * len[1])};
-        double d[3];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    double bx = 0.0, by = 0.0, bz = 0.0, bq = 0.0;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-          const int e = node_elem(g[c], PO, n);
-          d[c] = e + 0.5 + nodes.x[g[c] - PO * e] - xs[c];
+    for (int ax = 0; ax < 3; ++ax) {
+      const int t0 = ax == 0 ? 1 : 0, t1 = ax == 2 ? 1 : 2;   // the lower and higher tangential axis
+      for (int side = 0; side < 2; ++side) {
+        if (side == 0 ? Ec[ax] > nsr : (n - 1 - Ec[ax]) > nsr) continue;
+        // nodes on the faces of a lower axis were visited there
+        const int u0 = t0 < ax ? max(lo[t0], 1) : lo[t0], u1 = t0 < ax ? min(hi[t0], P - 2) : hi[t0];
+        const int v0 = t1 < ax ? max(lo[t1], 1) : lo[t1], v1 = t1 < ax ? min(hi[t1], P - 2) : hi[t1];
+        const int len = u1 - u0 + 1, count = len * (v1 - v0 + 1);
+        const size_t st0 = t0 == 0 ? 1 : P, st1 = t1 == 1 ? size_t(P) : size_t(P) * P;
+        const size_t sta = ax == 0 ? 1 : (ax == 1 ? size_t(P) : size_t(P) * P);
+        const double *mf = muc + (side ? size_t(P - 1) : size_t(0)) * sta + size_t(u0) * st0 + size_t(v0) * st1;
+        const double da = (side ? double(n) : 0.0) - xs[ax], da2 = da * da;
+        const double *pu = ps[t0] + (u0 - lo[t0]), *pv = ps[t1] + (v0 - lo[t1]);
+        const int dv = 64 / len, du = 64 - dv * len;
+        int v = lane / len, u = lane - v * len;
+        double m0 = 0.0, mu0 = 0.0, mv0 = 0.0;
+        for (int idx = lane; idx < count; idx += 64) {
+          const double mval = mf[size_t(u) * st0 + size_t(v) * st1];
+          const double d0 = pu[u] - xs[t0], d1 = pv[v] - xs[t1];
+          const double ri = rsqrt_pos(fma(d0, d0, fma(d1, d1, da2)));
+          const double q = mval * ri, w = q * ri * ri;
+          m0 += w;
+          mu0 = fma(w, d0, mu0);
+          mv0 = fma(w, d1, mv0);
+          bq += q;
+          u += du;
+          v += dv;
+          if (u >= len) {
+            u -= len;
+            ++v;
+          }
         }
-        const double mv = muc[(size_t(g[2]) * P + g[1]) * P + g[0]];
-        const double ri = 1.0 / sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-        const double w = mv * ri * ri * ri;
-        bx += w * d[0];
-        by += w * d[1];
-        bz += w * d[2];
-        bq += mv * ri;
+        const double fa = m0 * da;
+        if (ax == 0) { bx += fa; by += mu0; bz += mv0; }
+        else if (ax == 1) { bx += mu0; by += fa; bz += mv0; }
+        else { bx += mu0; by += mv0; bz += fa; }
       }
     }
     wave_sum4(bx, by, bz, bq);
@@ -797,8 +859,7 @@ int launch_box_apply(hipStream_t s, int P, int nb, int p, const double *Kc, cons
 
 int launch_box_bvals(hipStream_t s, int nb, int n, int nsr, int p, int64_t N, const BoxNodes &nodes, const int *start,
                      const double *sg, const double *sQ, const double *Wneg, double *phiB) {
-  const size_t P = size_t(p) * n + 1;
-  const int g = grid_of(size_t(nb) * 6 * P * P);
+  const int g = nb * 6 * n * n;
   switch (p) {
     case 4: hipLaunchKernelGGL(k_box_bvals<4>, dim3(g), dim3(256), 0, s, n, nsr, nb, N, nodes, start, sg, sQ, Wneg, phiB); return 0;
     case 5: hipLaunchKernelGGL(k_box_bvals<5>, dim3(g), dim3(256), 0, s, n, nsr, nb, N, nodes, start, sg, sQ, Wneg, phiB); return 0;

@@ -28,12 +28,6 @@ __global__ __launch_bounds__(256) void k_row_starts(int RT, int n, const int *__
     rowstart[r] = start[size_t(r) * n];
 }
 
-__device__ __forceinline__ double rsqrt_pos(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
-  const double e = fma(-x * y, y, 1.0);
-  return fma(0.5 * y, e, y);
-}
-
 // The staged x-range of one source row as up to three runs of sorted
 // charges: unwrapped elements u < 0 (image shift -1), 0 .. n - 1, >= n (+1).
 struct RowRuns {

@@ -259,15 +259,6 @@ __global__ __launch_bounds__(256) void k_moments(int n, int MT, int64_t N, const
 // One chunk of nt <= NT targets starting at sorted slot t0: every lane
 // walks its strided share of the block's sources and accumulates for all NT
 // targets in registers; the wave then reduces.
-// 1 / sqrt(x) for a positive normal x: the hardware estimate refined by one
-// Newton-Raphson step y <- y (3 - x y^2) / 2, written as y + y e / 2 with
-// e = 1 - x y^2 (one step squares the estimate's relative error).
-__device__ __forceinline__ double rsqrt_pos(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
-  const double e = fma(-x * y, y, 1.0);
-  return fma(0.5 * y, e, y);
-}
-
 template <int NSR, bool FORCE, int NT>
 __device__ __forceinline__ void pair_chunk(const PairSegments<NSR> &seg, int total, int lane, int64_t N, int t0,
                                            int nt, double nd, const double *__restrict__ sg,
