@@ -429,6 +429,8 @@ struct fep3m_ctx {
     return std_screen() ? launch_adj_moments(stream, nb, p, n, nsr, 1, gE, Tt, bxlam, gw, Aadj)
                         : launch_adj_g(stream, nb, n, nsr, p, span, nl, 1, gE, Tt, bxlam, gw, Aadj);
   }
+  double *upload_modes(const Mat &V, const char *what);
+  void box_modes(int P, const double *G, const double *lam, int i0, const double *in, double *a, double *b, double *out);
   void box_solve_neumann(double *f, double *sol, int which);
   void forward_box(double *Phi, double *U, bool pair_forces);
   void reverse_box(double *F, double *dUdQ);
@@ -1077,13 +1079,9 @@ void fep3m_ctx::build_box() {
     }
   Vec lamv;
   Mat V;
-  sym_gen_eig(Ki, Mi, lamv, V);
-  std::vector<double> vc(size_t(Pi) * Pi);
-  for (int i = 0; i < Pi; ++i)
-    for (int j = 0; j < Pi; ++j) vc[i + size_t(j) * Pi] = V(i, j);
-  bxV = alloc<double>(vc.size(), "box interior eigenvectors");
+  sym_gen_eig_parity(Ki, Mi, lamv, V);
+  bxV = upload_modes(V, "box interior eigenvectors");
   bxLam = alloc<double>(size_t(Pi), "box interior eigenvalues");
-  hip_check(hipMemcpy(bxV, vc.data(), vc.size() * sizeof(double), hipMemcpyHostToDevice), "upload");
   hip_check(hipMemcpy(bxLam, lamv.data(), size_t(Pi) * sizeof(double), hipMemcpyHostToDevice), "upload");
   const Vec nodes = gll_nodes(p);
   for (int a = 0; a <= p; ++a) bxnodes.x[a] = nodes[a];
@@ -1091,27 +1089,23 @@ void fep3m_ctx::build_box() {
   // the whole pencil K1 V = M1 V Lambda (one zero eigenvalue: the constants)
   Vec lf;
   Mat Vf;
-  sym_gen_eig(K1, M1, lf, Vf);
+  sym_gen_eig_parity(K1, M1, lf, Vf);
   bx_i0 = 0;
   for (int i = 1; i < Pb; ++i)
     if (std::fabs(lf[i]) < std::fabs(lf[bx_i0])) bx_i0 = i;
   lf[bx_i0] = 0.0;
-  std::vector<double> vf(size_t(Pb) * Pb), w1(Pb);
+  std::vector<double> w1(Pb);
   for (int i = 0; i < Pb; ++i) {
     double r = 0.0;
-    for (int j = 0; j < Pb; ++j) {
-      vf[i + size_t(j) * Pb] = Vf(i, j);
-      r += M1(i, j);
-    }
+    for (int j = 0; j < Pb; ++j) r += M1(i, j);
     w1[i] = r;
   }
-  bxVf = alloc<double>(vf.size(), "box pencil eigenvectors");
+  bxVf = upload_modes(Vf, "box pencil eigenvectors");
   bxLamf = alloc<double>(size_t(Pb), "box pencil eigenvalues");
   bxw1 = alloc<double>(size_t(Pb), "box mass row sums");
   bxtF = alloc<double>(size_t(nb) * 6 * n * n * (p + 1) * (p + 1), "box face loads");
   bxLw = alloc<double>(size_t(nb) * 6 * n * n * kBoxNQ * kBoxNQ, "box face adjoint weights");
   bxhF = alloc<double>(size_t(nb) * 6 * n * n * (p + 1) * (p + 1) * (p + 1), "box face adjoint moments");
-  hip_check(hipMemcpy(bxVf, vf.data(), vf.size() * sizeof(double), hipMemcpyHostToDevice), "upload");
   hip_check(hipMemcpy(bxLamf, lf.data(), size_t(Pb) * sizeof(double), hipMemcpyHostToDevice), "upload");
   hip_check(hipMemcpy(bxw1, w1.data(), size_t(Pb) * sizeof(double), hipMemcpyHostToDevice), "upload");
   Vec xq, wq;
@@ -1129,6 +1123,43 @@ void fep3m_ctx::build_box() {
   }
 }
 
+// The modes of a box's axis on the device, as the transforms read them.
+double *fep3m_ctx::upload_modes(const Mat &V, const char *what) {
+  const int P = V.r;
+  std::vector<double> v(size_t(P) * P);
+  for (int i = 0; i < P; ++i)
+    for (int j = 0; j < P; ++j) v[i + size_t(j) * P] = V(i, j);
+  if (parity_fits(P)) {
+    std::vector<double> g(parity_size(P));
+    parity_pack(P, v.data(), g.data());
+    v.swap(g);
+  }
+  double *d = alloc<double>(v.size(), what);
+  hip_check(hipMemcpy(d, v.data(), v.size() * sizeof(double), hipMemcpyHostToDevice), "upload");
+  return d;
+}
+
+// out = the pseudo-inverse of the Kronecker sum on P^3 nodes applied to in, by
+// its modes G with eigenvalues lam (null mode i0, or -1); a and b: work arrays
+// (in may be b).
+void fep3m_ctx::box_modes(int P, const double *G, const double *lam, int i0, const double *in, double *a, double *b,
+                          double *out) {
+  auto transform = [&](int axis, bool to_modes, const double *lams, const double *u, double *v) {
+    if (parity_fits(P)) {
+      launch_parity_transform(stream, P, axis, nb, G, to_modes, lams, i0, u, v);
+    } else {
+      launch_axis_transform(stream, P, axis, nb, G, to_modes, u, v);
+      if (lams) launch_fdm_scale(stream, size_t(P) * P * P * nb, P, i0, lams, v);
+    }
+  };
+  transform(0, true, nullptr, in, a);
+  transform(1, true, nullptr, a, b);
+  transform(2, true, lam, b, a);
+  transform(2, false, nullptr, a, b);
+  transform(1, false, nullptr, b, a);
+  transform(0, false, nullptr, a, out);
+}
+
 // Pure-Neumann solve of the insulating box on every node: f projected on
 // the compatible subspace (f -= (1^T f / V) M 1), then K^+ f by fast
 // diagonalisation of the whole box pencil with the constant mode dropped
@@ -1138,13 +1169,7 @@ void fep3m_ctx::box_solve_neumann(double *f, double *sol, int which) {
   int K = launch_box_resid(stream, Pb, nb, false, true, f, nullptr, partial);
   launch_sum_partials(stream, K, partial + size_t(nb) * K, pcs.zq, nb);   // 1^T f per configuration
   launch_box_sub_mass(stream, Pb, nb, 1.0 / (double(n) * n * n), bxw1, pcs.zq, f);
-  launch_axis_transform(stream, Pb, 0, nb, bxVf, true, f, bxt1);
-  launch_axis_transform(stream, Pb, 1, nb, bxVf, true, bxt1, bxt2);
-  launch_axis_transform(stream, Pb, 2, nb, bxVf, true, bxt2, bxt1);
-  launch_fdm_scale(stream, size_t(Pb) * Pb * Pb * nb, Pb, bx_i0, bxLamf, bxt1);
-  launch_axis_transform(stream, Pb, 2, nb, bxVf, false, bxt1, bxt2);
-  launch_axis_transform(stream, Pb, 1, nb, bxVf, false, bxt2, bxt1);
-  launch_axis_transform(stream, Pb, 0, nb, bxVf, false, bxt1, sol);
+  box_modes(Pb, bxVf, bxLamf, bx_i0, f, bxt1, bxt2, sol);
   K = launch_box_resid(stream, Pb, nb, false, false, f, nullptr, partial);
   launch_sum_partials(stream, K, partial, pcs.bn2, nb);
   box_apply(sol, bxy);
@@ -1199,13 +1224,7 @@ void fep3m_ctx::box_solve(const double *rhs, double *sol, int which, bool zero_b
     launch_box_axpby(stream, nv, 1.0, rhs, -1.0, bxy);        // r = rhs - K phi_B
     launch_box_interior(stream, Pb, nb, true, bxy, bxt1);
   }
-  launch_axis_transform(stream, Pi, 0, nb, bxV, true, bxt1, bxt2);
-  launch_axis_transform(stream, Pi, 1, nb, bxV, true, bxt2, bxt1);
-  launch_axis_transform(stream, Pi, 2, nb, bxV, true, bxt1, bxt2);
-  launch_fdm_scale(stream, ni, Pi, -1, bxLam, bxt2);        // no null mode
-  launch_axis_transform(stream, Pi, 2, nb, bxV, false, bxt2, bxt1);
-  launch_axis_transform(stream, Pi, 1, nb, bxV, false, bxt1, bxt2);
-  launch_axis_transform(stream, Pi, 0, nb, bxV, false, bxt2, bxt3);
+  box_modes(Pi, bxV, bxLam, -1, bxt1, bxt2, bxt1, bxt3);   // no null mode
   launch_box_interior(stream, Pb, nb, false, bxt3, sol);
   box_apply(sol, bxy);
   K = launch_box_resid(stream, Pb, nb, true, false, rhs, bxy, partial);

@@ -202,6 +202,42 @@ void sym_gen_eig(const Mat &K, const Mat &M, Vec &w, Mat &V) {
     }
 }
 
+void sym_gen_eig_parity(const Mat &K, const Mat &M, Vec &w, Mat &V) {
+  const int n = K.r, H = (n + 1) / 2;
+  w.assign(n, 0.0);
+  V = Mat(n, n);
+  for (int odd = 0; odd < 2; ++odd) {
+    const int m = odd ? n - H : H, at = odd ? H : 0;
+    const double sg = odd ? -1.0 : 1.0;
+    // in the basis (e_i + sg e_{n-1-i}) / sqrt 2 (the middle node by itself)
+    auto half = [&](const Mat &A) {
+      Mat B(m, m);
+      for (int i = 0; i < m; ++i)
+        for (int j = 0; j < m; ++j) {
+          const bool mi = 2 * i + 1 == n, mj = 2 * j + 1 == n;
+          if (mi && mj) B(i, j) = A(i, j);
+          else if (mi || mj) B(i, j) = std::sqrt(0.5) * (mi ? A(i, j) + A(i, n - 1 - j) : A(i, j) + A(n - 1 - i, j));
+          else B(i, j) = 0.5 * ((A(i, j) + A(n - 1 - i, n - 1 - j)) + sg * (A(i, n - 1 - j) + A(n - 1 - i, j)));
+        }
+      return B;
+    };
+    Vec wh;
+    Mat Vh;
+    sym_gen_eig(half(K), half(M), wh, Vh);
+    for (int j = 0; j < m; ++j) {
+      w[at + j] = wh[j];
+      for (int i = 0; i < m; ++i) {
+        if (2 * i + 1 == n) {
+          V(i, at + j) = Vh(i, j);
+        } else {
+          V(i, at + j) = std::sqrt(0.5) * Vh(i, j);
+          V(n - 1 - i, at + j) = sg * std::sqrt(0.5) * Vh(i, j);
+        }
+      }
+    }
+  }
+}
+
 Mat inverse(const Mat &A0) {
   const int n = A0.r;
   Mat A = A0, I(n, n);

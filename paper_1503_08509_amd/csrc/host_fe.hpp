@@ -36,6 +36,11 @@ void element_matrices(int p, Mat &ke, Mat &me);
 void sym_eig(const Mat &A, Vec &w, Mat &V);
 // Generalised symmetric-definite problem K v = lambda M v with V^T M V = I.
 void sym_gen_eig(const Mat &K, const Mat &M, Vec &w, Mat &V);
+// The same for a pencil that is symmetric under the reversal of its nodes
+// (the matrices of a box's axis): the (n + 1) / 2 modes even under it first,
+// then the odd ones, each in ascending order.  Two problems of half the size;
+// the modes' symmetry is exact.
+void sym_gen_eig_parity(const Mat &K, const Mat &M, Vec &w, Mat &V);
 // Dense inverse by Gauss-Jordan with partial pivoting.
 Mat inverse(const Mat &A);
 

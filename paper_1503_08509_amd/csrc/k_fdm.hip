@@ -475,6 +475,104 @@ __global__ __launch_bounds__(256) void k_axis_transform(int P, int axis, int nsy
   }
 }
 
+// The transforms of a box's axes, whose modes are even or odd under reversal.
+// With s_i = x_i + x_(P-1-i) and d_i = x_i - x_(P-1-i) (i < H = (P + 1) / 2;
+// the middle node's s is x itself, its d zero) the even modes need s alone and
+// the odd ones d, and backwards x_i and x_(P-1-i) are the sum and difference
+// of an even and an odd part: two products of half the size.
+//
+// A block of NW waves takes 16 lines: their halves stand in LDS, each wave
+// multiplies 16 x 16 tiles of both parts by float64 matrix-core steps (layout
+// as in k_axis_transform above), the matrices packed in the order the lanes read them,
+// [part][tile][step][lane].  Bound by memory and latency (16 us of copying and
+// 8 of products at P = 159, one array): 49 us per transform with the full
+// matrix in 64 x 64 tiles, 33 so (the division by eigenvalues included).  Along x the tile's rows are lines, so that
+// 16 consecutive outputs are stored together; else its columns.
+struct ParityShape {
+  int H, T, KS;   // half size, tiles of 16 outputs, steps of 4
+  __host__ __device__ explicit ParityShape(int P) : H((P + 1) / 2), T((H + 15) / 16), KS((H + 3) / 4) {}
+  __host__ __device__ size_t part() const { return size_t(T) * KS * 64; }
+};
+constexpr int kLineStride = 17;   // of the 16 lines' values in LDS: stores along x then hit all banks
+
+template <bool TO_MODES, bool AXIS0>
+__global__ __launch_bounds__(512) void k_parity_transform(int P, int axis, int nsys, const double *__restrict__ G,
+                                                          const double *__restrict__ lam, int i0,
+                                                          const double *__restrict__ in, double *__restrict__ out) {
+  extern __shared__ double plds[];
+  const ParityShape sh(P);
+  const int H = sh.H, H4 = 4 * sh.KS;
+  double *Xe = plds, *Xo = plds + H4 * kLineStride;
+  const size_t P2 = size_t(P) * P, per = P2 * P, lines = P2 * nsys, l0 = size_t(blockIdx.x) * 16;
+  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, r16 = lane & 15, kq = lane >> 4;
+  const size_t kst = AXIS0 ? 1 : (axis == 1 ? size_t(P) : P2);
+  auto line_base = [&](size_t l) -> size_t {   // address of element 0 of line l
+    const size_t sys = l / P2;
+    const int r = int(l - sys * P2);
+    if (AXIS0) return sys * per + size_t(r) * P;
+    if (axis == 1) return sys * per + size_t(r / P) * P2 + r % P;
+    return sys * per + r;
+  };
+  for (int i = tid; i < 16 * H4; i += nt) {
+    const int k = AXIS0 ? i % H4 : i / 16, l = AXIS0 ? i / H4 : i % 16;
+    double a = 0.0, b = 0.0;
+    if (k < H && l0 + l < lines) {
+      const double *x = in + line_base(l0 + l);
+      if (TO_MODES) {
+        const double u = x[size_t(k) * kst], v = x[size_t(P - 1 - k) * kst];
+        const bool mid = 2 * k + 1 == P;
+        a = mid ? u : u + v;
+        b = mid ? 0.0 : u - v;
+      } else {
+        a = x[size_t(k) * kst];
+        b = H + k < P ? x[size_t(H + k) * kst] : 0.0;
+      }
+    }
+    Xe[k * kLineStride + l] = a;
+    Xo[k * kLineStride + l] = b;
+  }
+  __syncthreads();
+  const double *Ge = G + (TO_MODES ? size_t(0) : 2 * sh.part()), *Go = Ge + sh.part();
+  for (int t = tid >> 6; t < sh.T; t += nt >> 6) {
+    f64x4 ae{0.0, 0.0, 0.0, 0.0}, ao{0.0, 0.0, 0.0, 0.0};
+    const double *ge = Ge + size_t(t) * sh.KS * 64 + lane, *go = Go + size_t(t) * sh.KS * 64 + lane;
+    const double *xe = Xe + kq * kLineStride + r16, *xo = Xo + kq * kLineStride + r16;
+#pragma unroll 5
+    for (int ks = 0; ks < sh.KS; ++ks) {
+      const double me = ge[ks * 64], mo = go[ks * 64];
+      const double ve = xe[4 * ks * kLineStride], vo = xo[4 * ks * kLineStride];
+      ae = AXIS0 ? __builtin_amdgcn_mfma_f64_16x16x4f64(ve, me, ae, 0, 0, 0)
+                 : __builtin_amdgcn_mfma_f64_16x16x4f64(me, ve, ae, 0, 0, 0);
+      ao = AXIS0 ? __builtin_amdgcn_mfma_f64_16x16x4f64(vo, mo, ao, 0, 0, 0)
+                 : __builtin_amdgcn_mfma_f64_16x16x4f64(mo, vo, ao, 0, 0, 0);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = kq + 4 * v;   // of the tile
+      const int o = 16 * t + (AXIS0 ? r16 : row);
+      const size_t l = l0 + (AXIS0 ? row : r16);
+      if (o >= H || l >= lines) continue;
+      double *y = out + line_base(l);
+      double a = ae[v], b = ao[v];
+      if (TO_MODES) {
+        const bool has = H + o < P;
+        if (lam) {
+          const int r = int(l % P2), x = r % P, yy = r / P;
+          const double lxy = lam[x] + lam[yy];
+          a = x == i0 && yy == i0 && o == i0 ? 0.0 : a / (lxy + lam[o]);
+          if (has) b = x == i0 && yy == i0 && H + o == i0 ? 0.0 : b / (lxy + lam[H + o]);
+        }
+        y[size_t(o) * kst] = a;
+        if (has) y[size_t(H + o) * kst] = b;
+      } else {
+        const bool mid = 2 * o + 1 == P;
+        y[size_t(o) * kst] = mid ? a : a + b;
+        if (!mid) y[size_t(P - 1 - o) * kst] = a - b;
+      }
+    }
+  }
+}
+
 inline int grid_of(size_t count) {
   size_t g = (count + 255) / 256;
   if (g < 1) g = 1;
@@ -522,6 +620,41 @@ void launch_axis_transform(hipStream_t s, int P, int axis, int nsys, const doubl
     hipLaunchKernelGGL((k_axis_transform<false, true>), dim3(grid), dim3(256), 0, s, P, axis, nsys, V, in, out);
   else
     hipLaunchKernelGGL((k_axis_transform<false, false>), dim3(grid), dim3(256), 0, s, P, axis, nsys, V, in, out);
+}
+
+// LDS holds both halves of 16 lines: P up to 1200
+bool parity_fits(int P) { return P >= 1 && size_t(4 * ParityShape(P).KS) * 2 * kLineStride * sizeof(double) <= 160 * 1024; }
+size_t parity_size(int P) { return 4 * ParityShape(P).part(); }
+
+void parity_pack(int P, const double *V, double *G) {
+  const ParityShape sh(P);
+  const int H = sh.H;
+  for (int dir = 0; dir < 2; ++dir)
+    for (int odd = 0; odd < 2; ++odd)
+      for (int t = 0; t < sh.T; ++t)
+        for (int ks = 0; ks < sh.KS; ++ks)
+          for (int l = 0; l < 64; ++l) {
+            const int k = 4 * ks + l / 16, o = 16 * t + l % 16;
+            const int node = dir ? o : k, mode = (dir ? k : o) + (odd ? H : 0);
+            const bool ok = node < H && (dir ? k : o) < (odd ? P - H : H) && !(odd && 2 * node + 1 == P);
+            *G++ = ok ? V[node + size_t(mode) * P] : 0.0;
+          }
+}
+
+void launch_parity_transform(hipStream_t s, int P, int axis, int nsys, const double *G, bool to_modes, const double *lam,
+                             int i0, const double *in, double *out) {
+  const ParityShape sh(P);
+  const unsigned grid = unsigned((size_t(P) * P * nsys + 15) / 16);
+  const int rounds = (sh.T + 7) / 8, nw = (sh.T + rounds - 1) / rounds;   // waves, at most eight
+  const size_t lds = size_t(4 * sh.KS) * 2 * kLineStride * sizeof(double);
+  if (to_modes && axis == 0)
+    hipLaunchKernelGGL((k_parity_transform<true, true>), dim3(grid), dim3(64 * nw), lds, s, P, axis, nsys, G, lam, i0, in, out);
+  else if (to_modes)
+    hipLaunchKernelGGL((k_parity_transform<true, false>), dim3(grid), dim3(64 * nw), lds, s, P, axis, nsys, G, lam, i0, in, out);
+  else if (axis == 0)
+    hipLaunchKernelGGL((k_parity_transform<false, true>), dim3(grid), dim3(64 * nw), lds, s, P, axis, nsys, G, lam, i0, in, out);
+  else
+    hipLaunchKernelGGL((k_parity_transform<false, false>), dim3(grid), dim3(64 * nw), lds, s, P, axis, nsys, G, lam, i0, in, out);
 }
 
 int launch_fs_solve(hipStream_t s, int nsys, int n, int p, const double *rhs, double *out, double2 *Z,

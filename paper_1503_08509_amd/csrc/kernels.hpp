@@ -240,6 +240,16 @@ int launch_fs_solve(hipStream_t s, int nsys, int n, int p, const double *rhs, do
 // V^T, else V.
 void launch_axis_transform(hipStream_t s, int P, int axis, int nsys, const double *V, bool to_modes, const double *in,
                            double *out);
+// The same with eigenvectors that are even (the first (P + 1) / 2 modes) or
+// odd under the reversal of an axis: half the products.  parity_pack lays
+// their matrix out for the kernel (column-major V as above); lam (with i0, or
+// null): the result of a transform into modes along z is divided by
+// lam[x] + lam[y] + lam[z], the entry i0 of all three (-1: none) set to zero.
+bool parity_fits(int P);
+size_t parity_size(int P);
+void parity_pack(int P, const double *V, double *G);
+void launch_parity_transform(hipStream_t s, int P, int axis, int nsys, const double *G, bool to_modes, const double *lam,
+                             int i0, const double *in, double *out);
 // FFT along one axis of [nb][z][y][x][nch] complex arrays in place, nch = p^3
 // (k_fft.hip); along x from nsys real mesh vectors, two to a complex array, and
 // back into them
