@@ -576,25 +576,23 @@ static MarchOp<T, PO> march_op(const LevelOpT<T> &op) {
 
 namespace {
 
-// A block's tile and march length.  Every system of a level uses the same
-// plan whether the forward and adjoint systems are solved together or alone
-// (nb configurations, up to 2 nb systems): the partial sums of the dot
-// products then add up in the same order.
+// A block's tile and march length.
 struct MarchPlan {
   int tx, ty, ze;
   int nx, ny, nz;   // blocks per system along each axis
   __host__ __device__ int blocks() const { return nx * ny * nz; }
 };
 
-MarchPlan plan_for(int n, int nb, int tx, int ty, int resident) {
+// The march length of least cost: rounds of resident blocks times the steps of
+// one (the start of a march costs 0.6 of a step: one element's planes and
+// carried rows), for sys systems.
+MarchPlan plan_for(int n, int sys, int tx, int ty, int resident) {
   MarchPlan best{};
   double cost = 1e300;
   for (int ze = 1; ze <= 16 && ze <= n; ++ze) {
     MarchPlan q{tx, ty, ze, (n + tx - 1) / tx, (n + ty - 1) / ty, (n + ze - 1) / ze};
-    // rounds of resident blocks times the steps of one (the start of a march
-    // costs 0.6 of a step: one element's planes and carried rows)
-    const double rounds = std::ceil(2.0 * nb * q.blocks() / resident);
-    const double c = (rounds < 4 ? rounds : 2.0 * nb * q.blocks() / resident + 0.5) * (ze + 0.6);
+    const double r = double(sys) * q.blocks() / resident, rounds = std::ceil(r);
+    const double c = (rounds < 4 ? rounds : r + 0.5) * (ze + 0.6);
     if (c < cost - 1e-9) {
       cost = c;
       best = q;
@@ -609,15 +607,28 @@ MarchPlan plan_for(int n, int nb, int tx, int ty, int resident) {
 // against 6.9; on 16^3 13.1 against 11.7).  Order 3: 4 x 4 columns 14.2
 // against 14.7 us for 8 x 4 on 32^3, 135 against 104 us on 64^3 (a Chebyshev
 // step), where their rows of 12 nodes leave half of each cache line to others.
-MarchPlan march_plan(int p, int n, int nb) {
+//
+// The length of the march suits the systems of the launch, except where sums
+// over a block follow from it (the dot products and the fused restriction,
+// shared): there a context of nb configurations keeps one plan, for 2 nb
+// systems, so that the forward and adjoint systems give the same bits solved
+// together or alone.  That plan leaves half of the chip idle for one system:
+// 30 us per launch at p = 5, 27^3, and 26 with its own length.  (A shared
+// length for both counts: 35 to 32 us for one system there, but 64 to 69 for
+// two on 32^3.)
+MarchPlan march_plan(int p, int n, int nb, int sys, bool shared) {
   const int64_t big = int64_t(2) * nb * ((n + 3) / 4) * ((n + 3) / 4) * n;   // blocks of 4 x 4 columns, one element each
+  if (shared) sys = 2 * nb;
   switch (p) {
-    case 3: return int64_t(2) * nb * n * n * n >= 131072 ? plan_for(n, nb, 8, 4, 512) : plan_for(n, nb, 4, 4, 1024);
-    case 4: return plan_for(n, nb, 4, 4, 512);
-    case 5: return big >= 384 ? plan_for(n, nb, 4, 4, 512) : plan_for(n, nb, 2, 2, 1024);
-    default: return plan_for(n, nb, 2, 2, 512);
+    case 3:
+      return int64_t(2) * nb * n * n * n >= 131072 ? plan_for(n, sys, 8, 4, 512) : plan_for(n, sys, 4, 4, 1024);
+    case 4: return plan_for(n, sys, 4, 4, 512);
+    case 5: return big >= 384 ? plan_for(n, sys, 4, 4, 512) : plan_for(n, sys, 2, 2, 1024);
+    default: return plan_for(n, sys, 2, 2, 512);
   }
 }
+
+MarchPlan shared_plan(int p, int n, int nb) { return march_plan(p, n, nb, nb, true); }
 
 template <class T, int PO, int TX, int TY, int NT, int WPS>
 int march_impl(hipStream_t s, int nsys, const MarchPlan &pl, const LevelOpT<T> &op, const TransferT<T> *tr, const T *x,
@@ -676,7 +687,8 @@ int march_impl(hipStream_t s, int nsys, const MarchPlan &pl, const LevelOpT<T> &
 template <class T>
 int march(hipStream_t s, int nb, int nsys, const LevelOpT<T> &op, const TransferT<T> *tr, const T *x, const T *f, T *out,
           const T *d, T *xo, T c1, T c2, int mode, double *partial, T s0) {
-  const MarchPlan pl = march_plan(op.p, op.n, nb);
+  const bool shared = mode == kApplyDot || mode == kChebDot || mode == kResidualNorm || mode == kResidualRestrict;
+  const MarchPlan pl = march_plan(op.p, op.n, nb, nsys, shared);
 #define FEP3M_TILE(PO, TX, TY, NT, W) \
   return march_impl<T, PO, TX, TY, NT, W>(s, nsys, pl, op, tr, x, f, out, d, xo, c1, c2, mode, partial, s0)
   switch (op.p * 10 + pl.tx) {
@@ -735,10 +747,10 @@ __global__ __launch_bounds__(256) void k_march_restrict_sum(MarchPlan pl, int n,
 
 }  // namespace
 
-int march_blocks(int p, int n, int nb) { return march_plan(p, n, nb).blocks(); }
+int march_blocks(int p, int n, int nb) { return shared_plan(p, n, nb).blocks(); }
 
 size_t march_restrict_size(int p, int n, int nb) {
-  const MarchPlan q = march_plan(p, n, nb);
+  const MarchPlan q = shared_plan(p, n, nb);
   return size_t(q.blocks()) * (3 * q.tx + 1) * (3 * q.ty + 1) * (3 * q.ze + 1);
 }
 
@@ -756,7 +768,7 @@ int launch_march_restrict(hipStream_t s, int nb, int nsys, const LevelOp &op, co
   if (K < 0) return K;
   const int Pc = 3 * op.n;
   hipLaunchKernelGGL(k_march_restrict_sum, dim3(unsigned(nsys) * Pc * Pc), dim3(Pc >= 256 ? 256 : 64 * ((Pc + 63) / 64)), 0,
-                     s, march_plan(op.p, op.n, nb), op.n, part, fc);
+                     s, shared_plan(op.p, op.n, nb), op.n, part, fc);
   return K;
 }
 
