@@ -231,7 +231,19 @@ __global__ __launch_bounds__(256) void k_fft_axis(int axis, const double2 *src, 
 //   ADJ: ZA(R k)[j] = (B^_2j + i B^_2j+1)(R k) * scale
 // Moments are indexed a = a_x + 2 a_y + 4 a_z (each 0 or 1), nodes
 // m = m_x + 6 (m_y + 6 m_z).
+//
+// Bound by memory (the spectrum, the transformed deposits and the field: 1.9
+// GB at 64^3, 0.38 ms at the copy rate) if the LDS reads of the products stay
+// below: a thread of the first product takes two frequencies of the orbit that
+// differ in k_x, which share their spectrum values (their node pairs swapped);
+// the second one is a 16 x 216 x 16 real product (moment and part of S by
+// frequency and part of the deposit), 54 float64 matrix-core steps over the
+// waves, on deposits stored under their reflected node.  One frequency per
+// thread and a thread per output of the second product read 0.66 MB of LDS
+// per orbit: 767 us; 482 so (130 and 66 us at 32^3).  Rows of 217 values keep the steps' 16 rows on
+// different banks.
 constexpr int kOrbitThreads = 512;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
 
 template <bool PSI, bool ADJ>
 __global__ __launch_bounds__(kOrbitThreads) void k_spec_orbit(int n, int NO, const double2 *__restrict__ S,
@@ -239,10 +251,11 @@ __global__ __launch_bounds__(kOrbitThreads) void k_spec_orbit(int n, int NO, con
                                                     const double2 *__restrict__ Zg, double2 *__restrict__ ZA,
                                                     double scale) {
   constexpr int Q1 = 6, NM = Q1 * Q1 * Q1, NC = NM / 2, NT = kOrbitThreads, NQ = NT / 64;
-  static_assert(NM % NQ == 0 && NQ * 64 <= 8 * NM, "node split of the transposed product");
-  __shared__ double2 Ss[8 * NM + 1];   // one spare slot
+  constexpr int NR = NM + 1;   // row stride
+  static_assert(NM % 4 == 0 && NQ * 256 <= 2 * 8 * NR, "steps of the transposed product");
+  __shared__ double2 Ss[8 * NR + 1];   // one spare slot
   __shared__ double2 Cs[8][8];
-  __shared__ double2 Gs[ADJ ? 8 * NM : 1];   // reused for the partial sums
+  __shared__ double2 Gs[ADJ ? 8 * NR : 1];   // reused for the partial sums
   const int H = n / 2 + 1;
   const int ko = blockIdx.x % NO, cfg = blockIdx.x / NO;
   const int kx = ko % H, ky = (ko / H) % H, kz = ko / (H * H);
@@ -271,7 +284,10 @@ __global__ __launch_bounds__(kOrbitThreads) void k_spec_orbit(int n, int NO, con
     for (int k = 0; k < KS; ++k) v[k] = Sk[min(tid + NT * k, 8 * NM - 1)];   // clamped: no branch per load
     asm volatile("" ::: "memory");   // compiler fence: all loads issue before the stores
 #pragma unroll
-    for (int k = 0; k < KS; ++k) Ss[min(tid + NT * k, 8 * NM)] = v[k];   // lanes past the end: spare slot
+    for (int k = 0; k < KS; ++k) {
+      const int i = tid + NT * k;
+      Ss[i < 8 * NM ? i + i / NM : 8 * NR] = v[k];   // lanes past the end: spare slot
+    }
   }
   if constexpr (PSI) if (tid < 64) {   // C^_a at each orbit frequency, from Z(f) and Z(-f)
     const int r = tid >> 3, a = tid & 7;
@@ -293,54 +309,74 @@ __global__ __launch_bounds__(kOrbitThreads) void k_spec_orbit(int n, int NO, con
     }
     asm volatile("" ::: "memory");
 #pragma unroll
-    for (int k = 0; k < KG; ++k) {   // slots outside the orbit are written but never read
+    for (int k = 0; k < KG; ++k) {   // rows outside the orbit are summed but not used
       const int i = min(tid + NT * k, 8 * NC - 1), r = i / NC, c = i % NC;
-      Gs[r * NM + 2 * c] = make_double2(0.5 * (z[k].x + zm[k].x), 0.5 * (z[k].y - zm[k].y));
-      Gs[r * NM + 2 * c + 1] = make_double2(0.5 * (z[k].y + zm[k].y), -0.5 * (z[k].x - zm[k].x));
+      Gs[r * NR + refl(2 * c, r)] = make_double2(0.5 * (z[k].x + zm[k].x), 0.5 * (z[k].y - zm[k].y));
+      Gs[r * NR + refl(2 * c + 1, r)] = make_double2(0.5 * (z[k].y + zm[k].y), -0.5 * (z[k].x - zm[k].x));
     }
   }
   __syncthreads();
   if constexpr (PSI) {
-    for (int i = tid; i < 8 * NC; i += NT) {
-      const int r = i / NC, c = i % NC;
+    for (int i = tid; i < 4 * NC; i += NT) {   // frequencies r and r + 1, channel c of the first
+      const int r = 2 * (i / NC), c = i % NC;
       if (r & ~pm) continue;
-      const int m0 = refl(2 * c, r), m1 = refl(2 * c + 1, r);
-      double2 P0 = make_double2(0.0, 0.0), P1 = make_double2(0.0, 0.0);
+      const int m0 = refl(2 * c, r), m1 = m0 + 1;   // S rows' pair; with k_x reversed nodes m1, m0 of channel c2
+      const int c2 = c - 2 * (c % (Q1 / 2)) + Q1 / 2 - 1;
+      double2 P0 = make_double2(0.0, 0.0), P1 = P0, R0 = P0, R1 = P0;
 #pragma unroll
       for (int a = 0; a < 8; ++a) {
+        const double2 s0 = Ss[a * NR + m0], s1 = Ss[a * NR + m1];
         const double sg = (__popc(a & r) & 1) ? -1.0 : 1.0;
         const double2 ch = make_double2(sg * Cs[r][a].x, sg * Cs[r][a].y);
-        P0 = cadd(P0, cmul(Ss[a * NM + m0], ch));
-        P1 = cadd(P1, cmul(Ss[a * NM + m1], ch));
+        P0 = cadd(P0, cmul(s0, ch));
+        P1 = cadd(P1, cmul(s1, ch));
+        const double sh = (a & 1) ? -sg : sg;
+        const double2 dh = make_double2(sh * Cs[r + 1][a].x, sh * Cs[r + 1][a].y);
+        R0 = cadd(R0, cmul(s1, dh));
+        R1 = cadd(R1, cmul(s0, dh));
       }
       Zpsi[(size_t(cfg) * M + fidx(r)) * NC + c] = make_double2((P0.x - P1.y) * scale, (P0.y + P1.x) * scale);
+      if (pm & 1)
+        Zpsi[(size_t(cfg) * M + fidx(r + 1)) * NC + c2] = make_double2((R0.x - R1.y) * scale, (R0.y + R1.x) * scale);
     }
   }
   if constexpr (ADJ) {
-    // 64 outputs (orbit member r, moment a) x NQ node ranges; the partial
-    // sums then go to Gs (no longer read) and are added in a fixed order
-    const int o = tid & 63, q = tid >> 6;
-    const int r = o >> 3, a = o & 7;
-    double2 acc = make_double2(0.0, 0.0);
-    if ((r & ~pm) == 0) {
-      constexpr int MQ = NM / NQ;
-      for (int m = q * MQ; m < (q + 1) * MQ; ++m) acc = cadd(acc, cmulc(Ss[a * NM + refl(m, r)], Gs[r * NM + m]));
-      if (__popc(a & r) & 1) acc = make_double2(-acc.x, -acc.y);
+    // D[2 a + s][2 r + g] = sum_m S_s[a][m] G_g[r][m], s and g the real (0) or
+    // imaginary part: every wave takes each NQ-th step of four nodes
+    const int lane = tid & 63, wave = tid >> 6, i16 = lane & 15, kq = lane >> 4;
+    const double *sp = reinterpret_cast<const double *>(Ss) + (i16 >> 1) * 2 * NR + 2 * kq + (i16 & 1);
+    const double *gp = reinterpret_cast<const double *>(Gs) + (i16 >> 1) * 2 * NR + 2 * kq + (i16 & 1);
+    f64x4 acc{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < (NM / 4 + NQ - 1) / NQ; ++k) {
+      const int ks = wave + NQ * k;
+      if (ks < NM / 4) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(sp[8 * ks], gp[8 * ks], acc, 0, 0, 0);
     }
     __syncthreads();
-    double2 *red = Gs;   // [q][64]
-    red[q * 64 + o] = acc;
-    __syncthreads();
-    if (tid < 32) {
-      const int rr = tid >> 2, j = tid & 3;
-      if ((rr & ~pm) == 0) {
-        double2 A0 = red[rr * 8 + 2 * j], A1 = red[rr * 8 + 2 * j + 1];
+    double *red = reinterpret_cast<double *>(Gs);   // [wave][row][column]
 #pragma unroll
-        for (int k = 1; k < NQ; ++k) {
-          A0 = cadd(A0, red[k * 64 + rr * 8 + 2 * j]);
-          A1 = cadd(A1, red[k * 64 + rr * 8 + 2 * j + 1]);
+    for (int v = 0; v < 4; ++v) red[wave * 256 + (kq + 4 * v) * 16 + i16] = acc[v];
+    __syncthreads();
+    double t = 0.0;
+    if (tid < 256) {
+#pragma unroll
+      for (int w = 0; w < NQ; ++w) t += red[w * 256 + tid];
+    }
+    double *D = reinterpret_cast<double *>(Ss);   // its rows are read
+    if (tid < 256) D[tid] = t;
+    __syncthreads();
+    if (tid < 32) {   // A0 + i A1 of moments 2 j and 2 j + 1, A = sum conj(S) G with the reflection's sign
+      const int r = tid >> 2, j = tid & 3;
+      if ((r & ~pm) == 0) {
+        double2 A[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          const int a = 2 * j + q;
+          const double sg = (__popc(a & r) & 1) ? -1.0 : 1.0;
+          const double *d = D + 2 * a * 16 + 2 * r;
+          A[q] = make_double2(sg * (d[0] + d[17]), sg * (d[1] - d[16]));
         }
-        ZA[(size_t(cfg) * M + fidx(rr)) * 4 + j] = make_double2((A0.x - A1.y) * scale, (A0.y + A1.x) * scale);
+        ZA[(size_t(cfg) * M + fidx(r)) * 4 + j] = make_double2((A[0].x - A[1].y) * scale, (A[0].y + A[1].x) * scale);
       }
     }
   }
