@@ -20,7 +20,7 @@
 // brick of 4 x 4 x 8 elements to one block, so small meshes left most compute
 // units idle: near field and moment adjoint together 2.9 ms at n = 27
 // (q = 3), 2.8 ms in a grounded box of 32^3, 4.9 ms for the 27-element q = 2
-// screen at n = 24; here 0.25, 0.46 and 0.33 ms.
+// screen at n = 24; here 0.29, 0.42 and 0.22 ms.
 #include "kernels.hpp"
 
 namespace fep3m {
@@ -301,13 +301,25 @@ __global__ __launch_bounds__(256) void k_conv_spec(int N, int NO, int nsr, int n
 // nodes, so every member uses the same spectrum value:
 //   Psi_r[R_r m] = sum_a S[a][m] sigma_r(a) C_r[a],
 //   B_r[a] = sigma_r(a) sum_m conj(S[a][m]) g_r[R_r m].
-// One thread per node (MB members each) for Psi, TPA lanes per moment for B.
+// Psi: one thread per node (MB members each).  B is a real product with 16
+// columns (member r, real or imaginary part) on the float64 matrix cores: 16
+// rows of (moment, part) per tile, summed over the nodes, the spectrum values
+// read from memory as the left operand, the nodes split over the waves that
+// the tiles leave.  16 lanes per moment instead, with a chain of loads each:
+// 175 us in a box of 32^3, 96 so; both products of the 27-element q = 2 screen
+// at 24^3 174 and 83 us.  (Psi by matrix-core steps too: 62 to 88 us in that
+// box, whose 8 moments make four steps of a tile.)
 struct ConvProd {
   int N, NO, p, nl, na, M, CHc, CHm;
+  int MR;   // row stride of the nodes' values in LDS
   double scale;
   const double2 *S, *zc, *zg;
   double2 *zpsi, *za;
 };
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+__host__ __device__ constexpr int conv_tiles(int na) { return (2 * na + 15) / 16; }
+__host__ __device__ constexpr int conv_split(int tiles) { return tiles >= 3 ? 1 : 4 / tiles; }   // waves that share a tile
 
 template <int MB>
 __device__ __forceinline__ void conv_psi(const ConvProd &a, const double2 *Sk, const double2 *Cs, double2 *Ps, int m, int r0,
@@ -329,7 +341,7 @@ __device__ __forceinline__ void conv_psi(const ConvProd &a, const double2 *Sk, c
   for (int r = 0; r < MB; ++r) {
     const int q = r0 + r;
     const int t = (((q & 4) ? q1 - 1 - mz : mz) * q1 + ((q & 2) ? q1 - 1 - my : my)) * q1 + ((q & 1) ? q1 - 1 - mx : mx);
-    Ps[q * a.M + t] = acc[r];
+    Ps[q * a.MR + t] = acc[r];
   }
 }
 
@@ -337,9 +349,9 @@ template <bool PSI, bool ADJ>
 __global__ __launch_bounds__(256) void k_conv_prod(ConvProd a) {
   extern __shared__ double2 lds[];
   double2 *Cs = lds;                                  // [na][8]: sigma_r C_r
-  double2 *Bs = Cs + (PSI ? 8 * a.na : 0);            // [8][na]
-  double2 *Gs = Bs + (ADJ ? 8 * a.na : 0);            // [8][M]: g_r at R_r m; then Psi_r
-  const int N = a.N, H = N / 2 + 1, tid = threadIdx.x;
+  double *Gs = reinterpret_cast<double *>(Cs + (PSI ? 8 * a.na : 0));   // [8][MR][2]: g_r at R_r m; then Psi_r
+  double *Ds = Gs + 16 * a.MR;                        // [split][tiles][16][16]: S by g
+  const int N = a.N, H = N / 2 + 1, tid = threadIdx.x, M = a.M, MR = a.MR;
   const int nb = gridDim.x / a.NO, cfg = blockIdx.x % nb, ko = blockIdx.x / nb;   // a frequency's configurations in turn
   const int kx = ko % H, ky = (ko / H) % H, kz = ko / (H * H);
   const int q1 = a.p + 1;
@@ -353,10 +365,14 @@ __global__ __launch_bounds__(256) void k_conv_prod(ConvProd a) {
     const int x = (r & 1) ? N - kx : kx, y = (r & 2) ? N - ky : ky, z = (r & 4) ? N - kz : kz;
     return size_t(cfg) * N3 + (size_t(z) * N + y) * N + x;
   };
-  const double2 *Sk = a.S + size_t(ko) * a.na * a.M;
+  const double2 *Sk = a.S + size_t(ko) * a.na * M;
   auto sigma = [&](int i, int r) {
     const int ax = i % a.nl, ay = (i / a.nl) % a.nl, az = i / (a.nl * a.nl);
     return (((r & 1) & ax) ^ ((r >> 1) & ay & 1) ^ ((r >> 2) & az & 1)) & 1 ? -1.0 : 1.0;
+  };
+  auto refl = [&](int m, int r) {
+    const int mx = m % q1, my = (m / q1) % q1, mz = m / (q1 * q1);
+    return (((r & 4) ? q1 - 1 - mz : mz) * q1 + ((r & 2) ? q1 - 1 - my : my)) * q1 + ((r & 1) ? q1 - 1 - mx : mx);
   };
   if constexpr (PSI) {   // unpack the real channels' transforms: Z(f), Z(-f)
     for (int i = tid; i < 8 * a.na; i += 256) {
@@ -373,66 +389,64 @@ __global__ __launch_bounds__(256) void k_conv_prod(ConvProd a) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int m = 2 * c + h;
-        if (m >= a.M) continue;
-        const int mx = m % q1, my = (m / q1) % q1, mz = m / (q1 * q1);
-        const int t = (((r & 4) ? q1 - 1 - mz : mz) * q1 + ((r & 2) ? q1 - 1 - my : my)) * q1 + ((r & 1) ? q1 - 1 - mx : mx);
-        Gs[r * a.M + t] = h ? make_double2(0.5 * (z.y + zm.y), -0.5 * (z.x - zm.x)) : make_double2(0.5 * (z.x + zm.x), 0.5 * (z.y - zm.y));
+        if (m >= M) continue;
+        double *g = Gs + 2 * (r * MR + refl(m, r));
+        g[0] = h ? 0.5 * (z.y + zm.y) : 0.5 * (z.x + zm.x);
+        g[1] = h ? -0.5 * (z.x - zm.x) : 0.5 * (z.y - zm.y);
       }
     }
+    for (int i = tid; i < 16 * (MR - M); i += 256) Gs[2 * ((i >> 1) / (MR - M) * MR + M + (i >> 1) % (MR - M)) + (i & 1)] = 0.0;
   }
   __syncthreads();
   if constexpr (ADJ) {
-    constexpr int TPA = 16;
-    for (int i0 = 0; i0 < a.na; i0 += 256 / TPA) {
-      const int i = i0 + tid / TPA, lane = tid % TPA;
-      double2 acc[8];
-#pragma unroll
-      for (int r = 0; r < 8; ++r) acc[r] = make_double2(0.0, 0.0);
-      if (i < a.na)
-        for (int m = lane; m < a.M; m += TPA) {
-          const double2 s = Sk[size_t(i) * a.M + m];
-#pragma unroll
-          for (int r = 0; r < 8; ++r) {
-            const double2 g = Gs[r * a.M + m];
-            acc[r].x += s.x * g.x + s.y * g.y;
-            acc[r].y += s.x * g.y - s.y * g.x;
-          }
-        }
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-#pragma unroll
-        for (int o = TPA / 2; o > 0; o >>= 1) {
-          acc[r].x += __shfl_xor(acc[r].x, o, 64);
-          acc[r].y += __shfl_xor(acc[r].y, o, 64);
-        }
+    const int lane = tid & 63, wave = tid >> 6, i16 = lane & 15, kq = lane >> 4;
+    const int tiles = conv_tiles(a.na), split = conv_split(tiles), steps = (M + 3) / 4;
+    for (int u = wave; u < tiles * split; u += 4) {
+      const int t = u % tiles, part = u / tiles;
+      const int row = min(16 * t + i16, 2 * a.na - 1);   // rows past the last are not used
+      const double *s = reinterpret_cast<const double *>(Sk + size_t(row >> 1) * M) + (row & 1), *g = Gs + (i16 >> 1) * 2 * MR + (i16 & 1);
+      f64x4 acc{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+      for (int ks = part; ks < steps; ks += split) {
+        const int m = 4 * ks + kq;
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(s[2 * min(m, M - 1)], g[2 * m], acc, 0, 0, 0);
       }
-      if (i < a.na && lane < 8) {
-        double2 v = acc[0];
 #pragma unroll
-        for (int r = 1; r < 8; ++r) v = lane == r ? acc[r] : v;
-        const double g = sigma(i, lane);
-        Bs[lane * a.na + i] = make_double2(g * v.x, g * v.y);
-      }
+      for (int v = 0; v < 4; ++v) Ds[(part * tiles + t) * 256 + (kq + 4 * v) * 16 + i16] = acc[v];
     }
     __syncthreads();
     for (int i = tid; i < 8 * a.CHc; i += 256) {
       const int r = i / a.CHc, c = i % a.CHc;
       if (r & ~pm) continue;
-      const double2 u = Bs[r * a.na + 2 * c], v = 2 * c + 1 < a.na ? Bs[r * a.na + 2 * c + 1] : make_double2(0.0, 0.0);
-      a.za[fidx(r) * a.CHc + c] = make_double2((u.x - v.y) * a.scale, (u.y + v.x) * a.scale);
+      double2 B[2];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int j = 2 * c + h;
+        double re = 0.0, im = 0.0;
+        if (j < a.na)
+          for (int part = 0; part < split; ++part) {
+            const double *d = Ds + part * tiles * 256 + 2 * j * 16 + 2 * r;
+            re += d[0] + d[17];
+            im += d[1] - d[16];
+          }
+        const double g = j < a.na ? sigma(j, r) : 0.0;
+        B[h] = make_double2(g * re, g * im);
+      }
+      a.za[fidx(r) * a.CHc + c] = make_double2((B[0].x - B[1].y) * a.scale, (B[0].y + B[1].x) * a.scale);
     }
   }
-  if constexpr (PSI) {
+  if constexpr (PSI) {   // Gs was last read before the barrier above
     // threads beyond one per node share a node's members
-    if (a.M <= 64) conv_psi<2>(a, Sk, Cs, Gs, min(tid & 63, a.M - 1), 2 * (tid >> 6), q1);
-    else if (a.M <= 128) conv_psi<4>(a, Sk, Cs, Gs, min(tid & 127, a.M - 1), 4 * (tid >> 7), q1);
+    double2 *Ps = reinterpret_cast<double2 *>(Gs);
+    if (M <= 64) conv_psi<2>(a, Sk, Cs, Ps, min(tid & 63, M - 1), 2 * (tid >> 6), q1);
+    else if (M <= 128) conv_psi<4>(a, Sk, Cs, Ps, min(tid & 127, M - 1), 4 * (tid >> 7), q1);
     else
-      for (int m = tid; m < a.M; m += 256) conv_psi<8>(a, Sk, Cs, Gs, m, 0, q1);
+      for (int m = tid; m < M; m += 256) conv_psi<8>(a, Sk, Cs, Ps, m, 0, q1);
     __syncthreads();
     for (int i = tid; i < 8 * a.CHm; i += 256) {
       const int r = i / a.CHm, c = i % a.CHm;
       if (r & ~pm) continue;
-      const double2 u = Gs[r * a.M + 2 * c], v = 2 * c + 1 < a.M ? Gs[r * a.M + 2 * c + 1] : make_double2(0.0, 0.0);
+      const double2 u = Ps[r * MR + 2 * c], v = 2 * c + 1 < M ? Ps[r * MR + 2 * c + 1] : make_double2(0.0, 0.0);
       a.zpsi[fidx(r) * a.CHm + c] = make_double2((u.x - v.y) * a.scale, (u.y + v.x) * a.scale);
     }
   }
@@ -564,7 +578,10 @@ void launch_conv_products(hipStream_t s, const ConvPlan &c, int nb, const double
   a.zpsi = c.zpsi;
   a.za = c.za;
   const dim3 grid(unsigned(a.NO) * nb);
-  const size_t lds = (size_t(8) * c.na * ((C ? 1 : 0) + (gE ? 1 : 0)) + size_t(8) * c.M) * sizeof(double2);
+  a.MR = (c.M + 3) / 4 * 4 | 1;   // odd: the members' rows on different banks
+  const int tiles = conv_tiles(c.na);
+  const size_t lds = ((C ? size_t(16) * c.na : 0) + size_t(16) * a.MR + (gE ? size_t(256) * tiles * conv_split(tiles) : 0)) *
+                     sizeof(double);
   if (C && gE) hipLaunchKernelGGL((k_conv_prod<true, true>), grid, dim3(256), lds, s, a);
   else if (C) hipLaunchKernelGGL((k_conv_prod<true, false>), grid, dim3(256), lds, s, a);
   else hipLaunchKernelGGL((k_conv_prod<false, true>), grid, dim3(256), lds, s, a);
