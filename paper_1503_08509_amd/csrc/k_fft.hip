@@ -323,17 +323,21 @@ __global__ __launch_bounds__(kOrbitThreads) void k_spec_orbit(int n, int NO, con
       const int m0 = refl(2 * c, r), m1 = m0 + 1;   // S rows' pair; with k_x reversed nodes m1, m0 of channel c2
       const int c2 = c - 2 * (c % (Q1 / 2)) + Q1 / 2 - 1;
       double2 P0 = make_double2(0.0, 0.0), P1 = P0, R0 = P0, R1 = P0;
+      auto mac = [](double2 &P, double2 s, double2 ch) {   // P += s ch with its roundings spelled out: the float32
+        P.x += fma(s.x, ch.x, -(s.y * ch.y));              // element field of mixed precision follows from the sum,
+        P.y += fma(s.x, ch.y, s.y * ch.x);                 // and a last bit can move its rounding
+      };
 #pragma unroll
       for (int a = 0; a < 8; ++a) {
         const double2 s0 = Ss[a * NR + m0], s1 = Ss[a * NR + m1];
         const double sg = (__popc(a & r) & 1) ? -1.0 : 1.0;
         const double2 ch = make_double2(sg * Cs[r][a].x, sg * Cs[r][a].y);
-        P0 = cadd(P0, cmul(s0, ch));
-        P1 = cadd(P1, cmul(s1, ch));
+        mac(P0, s0, ch);
+        mac(P1, s1, ch);
         const double sh = (a & 1) ? -sg : sg;
         const double2 dh = make_double2(sh * Cs[r + 1][a].x, sh * Cs[r + 1][a].y);
-        R0 = cadd(R0, cmul(s1, dh));
-        R1 = cadd(R1, cmul(s0, dh));
+        mac(R0, s1, dh);
+        mac(R1, s0, dh);
       }
       Zpsi[(size_t(cfg) * M + fidx(r)) * NC + c] = make_double2((P0.x - P1.y) * scale, (P0.y + P1.x) * scale);
       if (pm & 1)
