@@ -149,7 +149,7 @@ enum {
                              a little more) is a product of two factors up to
                              11 or 13: the same maps by mixed-radix transforms,
                              any screen family, any boundary.  Else (mixed
-                             precision, larger n, a spectrum above 16 GB or
+                             precision, larger n, a spectrum above 32 GB or
                              more than memory holds) DIRECT                      */
   FEP3M_NEAR_DIRECT = 1,  /* the table sums themselves: 2 * 8 * (p+1)^3 FLOP per
                              element and near offset (matrix cores forward,

@@ -736,16 +736,19 @@ void fep3m_ctx::build_mg() {
 // The convolution's plan, spectrum and work arrays, where near_field = AUTO
 // leaves the choice, in float64 (the table sums of mixed precision are
 // float32).  The table sums stay where the lattice has no plan, where the
-// spectrum would exceed kConvSpecMax (27-element q = 4 screens above 56^3;
-// the others stay below 8 GB at 64^3), and where its memory is not to be had.
-constexpr size_t kConvSpecMax = size_t(16) << 30;
+// spectrum would exceed kConvSpecMax, and where its memory is not to be had.
+// At 64^3 the 27-element q = 4 screens' takes 25 GB (399 ms per call with 10^6
+// charges by the table sums, 127 so), every other family's less than 8.
+constexpr size_t kConvSpecMax = size_t(32) << 30;
 void fep3m_ctx::build_conv() {
   if (mixed || opt.near_field != FEP3M_NEAR_AUTO || !conv_plan(n, nsr, p, nl, box, cv)) return;
   const size_t N3 = size_t(cv.N) * cv.N * cv.N * nb, cc = (cv.na + 1) / 2, cm = (cv.M + 1) / 2;
   const size_t ns = conv_spec_size(cv);
   if (ns * sizeof(double2) > kConvSpecMax) return;
   const size_t want = (ns + N3 * 2 * (cc + cm) + cv.N) * sizeof(double2) + 6 * 512;
-  if (arena && arena_used + want > kStaticBytes) return;
+  // static storage also keeps room for the staging buffers of graph mode
+  const size_t staging = opt.use_graph ? (9 * size_t(N) + nb) * sizeof(double) + 6 * 512 : 0;
+  if (arena && arena_used + want + staging > kStaticBytes) return;
   const size_t held = allocs.size(), bytes = dev_bytes;
   try {
     cv.tw = alloc<double2>(size_t(cv.N), "lattice twiddles");
