@@ -444,13 +444,19 @@ __global__ __launch_bounds__(256) void k_box_charge_bnd(int n, int nsr, int nb, 
 // the higher tangential axis, kc along the lower).  Faces: f = a 2 n^2 +
 // s n^2 + j n + i (axis a, side s, tangential element indices i lower, j
 // higher).
+// The near block's charges are staged in LDS and split over two groups of
+// threads: bound by the arithmetic of the pairs.  Read one after the other
+// from memory by 100 threads they took 3.65 ms at 64^3 elements with 10^6
+// charges; 2.05 so.
 template <int PO>
-__global__ __launch_bounds__(128) void k_box_flux(int n, int nsr, int64_t N, BoxQuad qd, const int *__restrict__ start,
+__global__ __launch_bounds__(256) void k_box_flux(int n, int nsr, int64_t N, BoxQuad qd, const int *__restrict__ start,
                                                   const double *__restrict__ sg, const double *__restrict__ sQ,
                                                   const double *__restrict__ Wneg, double *__restrict__ tF) {
-  constexpr int Q1 = PO + 1, NM = Q1 * Q1 * Q1, NQ = kBoxNQ;
-  __shared__ double fl[NQ * NQ];
-  const int nf = 6 * n * n;
+  constexpr int Q1 = PO + 1, NM = Q1 * Q1 * Q1, NQ = kBoxNQ, NQ2 = NQ * NQ, CAP = 512, RM = 49, G = 256 / NQ2;
+  __shared__ double4 ch[CAP];
+  __shared__ double fl[G * NQ2], xq[NQ];
+  __shared__ int rb[RM], pre[RM + 1];
+  const int nf = 6 * n * n, tid = threadIdx.x;
   const int cfg = blockIdx.x / nf, f = blockIdx.x % nf;
   const int a = f / (2 * n * n), side = (f / (n * n)) % 2, i = f % n, j = (f / n) % n;
   const int t0 = a == 0 ? 1 : 0, t1 = a == 2 ? 1 : 2;
@@ -462,30 +468,52 @@ __global__ __launch_bounds__(128) void k_box_flux(int n, int nsr, int64_t N, Box
   const size_t cbase = size_t(cfg) * M;
   const size_t E = cbase + e[0] + size_t(n) * (e[1] + size_t(n) * e[2]);
   const double sgn = side ? 1.0 : -1.0;
-  const int q = threadIdx.x;
-  if (q < NQ * NQ) {
-    const int qi = q / NQ, qj = q % NQ;   // qi along t1, qj along t0
-    double X[3];
-    X[a] = side ? double(n) : 0.0;
-    X[t0] = e[t0] + 0.5 + qd.xq[qj];
-    X[t1] = e[t1] + 0.5 + qd.xq[qi];
-    double dn = 0.0;   // n . grad of sum_j Q_j / |x - y_j|
-    for (int dz = -nsr; dz <= nsr; ++dz) {
-      const int sz = e[2] + dz;
-      if (sz < 0 || sz >= n) continue;
-      for (int dy = -nsr; dy <= nsr; ++dy) {
-        const int sy = e[1] + dy;
-        if (sy < 0 || sy >= n) continue;
-        const int sx0 = max(e[0] - nsr, 0), sx1 = min(e[0] + nsr, n - 1);
-        const size_t row = cbase + size_t(n) * (sy + size_t(n) * sz);
-        for (int s = start[row + sx0]; s < start[row + sx1 + 1]; ++s) {
-          const double d0 = X[0] - sg[s], d1 = X[1] - sg[N + s], d2 = X[2] - sg[2 * N + s];
-          const double ri = 1.0 / sqrt(d0 * d0 + d1 * d1 + d2 * d2);
-          const double da = a == 0 ? d0 : (a == 1 ? d1 : d2);
-          dn -= sQ[s] * da * ri * ri * ri;
-        }
+  const int y0 = max(e[1] - nsr, 0), ny = min(e[1] + nsr, n - 1) - y0 + 1;
+  const int z0 = max(e[2] - nsr, 0), nz = min(e[2] + nsr, n - 1) - z0 + 1;
+  const int x0 = max(e[0] - nsr, 0), x1 = min(e[0] + nsr, n - 1), rows = ny * nz;
+  if (tid < NQ) xq[tid] = qd.xq[tid];
+  if (tid < rows) {   // the elements x0 .. x1 of one row are consecutive in the sorted order
+    const size_t row = cbase + size_t(n) * (y0 + tid % ny + size_t(n) * (z0 + tid / ny));
+    rb[tid] = start[row + x0];
+    pre[tid + 1] = start[row + x1 + 1] - rb[tid];
+  }
+  __syncthreads();
+  if (tid == 0) {
+    pre[0] = 0;
+    for (int r = 0; r < rows; ++r) pre[r + 1] += pre[r];
+  }
+  __syncthreads();
+  const int total = pre[rows], grp = tid / NQ2, q = tid - grp * NQ2, qi = q / NQ, qj = q % NQ;   // qi along t1, qj along t0
+  double X[3];
+  X[a] = side ? double(n) : 0.0;
+  X[t0] = e[t0] + 0.5 + xq[qj];
+  X[t1] = e[t1] + 0.5 + xq[qi];
+  double dn = 0.0;   // n . grad of sum_j Q_j / |x - y_j|
+  for (int c0 = 0; c0 < total; c0 += CAP) {
+    if (c0 > 0) __syncthreads();   // the chunk before is read
+    for (int r = tid >> 6; r < rows; r += 4) {
+      const int lo = max(pre[r], c0), hi = min(pre[r + 1], c0 + CAP);
+      for (int k = lo + (tid & 63); k < hi; k += 64) {
+        const int s = rb[r] + k - pre[r];
+        ch[k - c0] = make_double4(sg[s], sg[N + s], sg[2 * N + s], sQ[s]);
       }
     }
+    __syncthreads();
+    if (grp < G) {
+      const int m = min(CAP, total - c0);
+      for (int k = grp; k < m; k += G) {
+        const double4 c = ch[k];
+        const double d0 = X[0] - c.x, d1 = X[1] - c.y, d2 = X[2] - c.z;
+        const double ri = rsqrt_pos(fma(d0, d0, fma(d1, d1, d2 * d2)));
+        const double da = a == 0 ? d0 : (a == 1 ? d1 : d2);
+        dn -= c.w * da * (ri * ri * ri);
+      }
+    }
+  }
+  if (grp < G) fl[tid] = dn;
+  __syncthreads();
+  if (tid < NQ2) {
+    for (int g = 1; g < G; ++g) dn += fl[g * NQ2 + tid];
     dn *= sgn;
     // n . grad Psi = -n . grad Wneg from the element's nodal values
     const double *w = Wneg + E * NM;
@@ -495,11 +523,11 @@ __global__ __launch_bounds__(128) void k_box_flux(int n, int nsr, int64_t N, Box
       dpsi -= w[m] * qd.dend[side][k[a]] * qd.lq[qi][k[t1]] * qd.lq[qj][k[t0]];
     }
     dpsi *= sgn;
-    fl[q] = (dn - dpsi) * qd.wq[qi] * qd.wq[qj];
+    fl[q] = (dn - dpsi) * qd.wq[qi] * qd.wq[qj];   // its own slot, read above by this thread alone
   }
   __syncthreads();
-  if (q < Q1 * Q1) {
-    const int kb = q / Q1, kc = q % Q1;
+  if (tid < Q1 * Q1) {
+    const int kb = tid / Q1, kc = tid % Q1;
     double v = 0.0;
     for (int qi = 0; qi < NQ; ++qi)
       for (int qj = 0; qj < NQ; ++qj) v += fl[qi * NQ + qj] * qd.lq[qi][kb] * qd.lq[qj][kc];
@@ -586,8 +614,12 @@ __global__ __launch_bounds__(256) void k_box_h_slots(int n, int nb, const double
 // sum over the face's Gauss points of Lw (-n / r^3 + 3 (n.d) d / r^5) and of
 // Lw (n.d) / r^3 (d = x_q - x_s); F -= Q s2 / 2 times the first, dU/dQ +=
 // inv_h / 2 times the second (physical units, caller order).  One wave per
-// charge: the lanes split the (face element, Gauss point) pairs of each
-// near face and the wave sums them.
+// charge: the lanes split the Gauss points of each near face and the wave
+// sums them.  Bound by the arithmetic of the points: a lane steps (row,
+// column) without division by a run-time value, takes the coordinates from
+// the wave's table and sums w / r^3, w / r^5 and the tangential moments of the
+// latter (5.21 ms at 64^3 elements with 10^6 charges when each point was
+// worked out from its index; 2.48 so).
 template <int PO>
 __global__ __launch_bounds__(256) void k_box_flux_charge(int n, int nsr, int nb, int64_t N,
                                                          const int *__restrict__ off, double inv_h, BoxQuad qd,
@@ -595,6 +627,11 @@ __global__ __launch_bounds__(256) void k_box_flux_charge(int n, int nsr, int nb,
                                                          const double *__restrict__ Lw, const int *__restrict__ perm,
                                                          double *__restrict__ F, double *__restrict__ dUdQ) {
   constexpr int NQ = kBoxNQ, NQ2 = NQ * NQ;
+  constexpr int LM = 7 * NQ;   // points of seven elements (n_sr <= 3)
+  __shared__ double pos[4][3][LM], xq[NQ];
+  if (threadIdx.x < NQ) xq[threadIdx.x] = qd.xq[threadIdx.x];
+  __syncthreads();
+  double(&ps)[3][LM] = pos[threadIdx.x >> 6];
   const size_t nf = size_t(6) * n * n;
   const int lane = threadIdx.x & 63;
   const int64_t waves = int64_t(gridDim.x) * (blockDim.x >> 6);
@@ -605,35 +642,60 @@ __global__ __launch_bounds__(256) void k_box_flux_charge(int n, int nsr, int nb,
     for (int c = 0; c < 3; ++c) Ec[c] = min(int(floor(xs[c])), n - 1);
     if (far_from_faces(Ec, n, nsr)) continue;
     const int cfg = cfg_of(off, nb, s);
+    // along each axis the Gauss points of the near block's elements: their
+    // coordinates and their parts of the weights' address (the wave's own
+    // tables: its accesses stay in order)
+    int lo[3], len[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      lo[c] = max(Ec[c] - nsr, 0);
+      len[c] = (min(Ec[c] + nsr, n - 1) - lo[c] + 1) * NQ;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (int k = lane; k < LM; k += 64)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) ps[c][k] = lo[c] + k / NQ + 0.5 + xq[k % NQ];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     double gx = 0.0, gy = 0.0, gz = 0.0, dq = 0.0;
+#pragma unroll
     for (int a = 0; a < 3; ++a) {
       const int t0 = a == 0 ? 1 : 0, t1 = a == 2 ? 1 : 2;
       for (int side = 0; side < 2; ++side) {
         if (side == 0 ? Ec[a] > nsr : (n - 1 - Ec[a]) > nsr) continue;
         const double sgn = side ? 1.0 : -1.0;
-        const double da = (side ? double(n) : 0.0) - xs[a];   // normal offset, the same at every point
-        const int i0 = max(Ec[t0] - nsr, 0), i1 = min(Ec[t0] + nsr, n - 1);
-        const int j0 = max(Ec[t1] - nsr, 0), j1 = min(Ec[t1] + nsr, n - 1);
-        const int ni = i1 - i0 + 1, count = ni * (j1 - j0 + 1) * NQ2;
-        const double *lwp = Lw + (size_t(cfg) * nf + size_t(a) * 2 * n * n + size_t(side) * n * n) * NQ2;
+        const double da = (side ? double(n) : 0.0) - xs[a], da2 = da * da;   // normal offset, the same at every point
+        const double *lwp = Lw + (size_t(cfg) * nf + size_t(a) * 2 * n * n + size_t(side) * n * n) * NQ2 +
+                            (size_t(lo[t1]) * n + lo[t0]) * NQ2;
+        const int count = len[t0] * len[t1], dv = 64 / len[t0], du = 64 - dv * len[t0];
+        int v = lane / len[t0], u = lane - v * len[t0];
+        double s3 = 0.0, s5 = 0.0, m0 = 0.0, m1 = 0.0;   // sums of w / r^3, w / r^5 and of the latter's tangential moments
         for (int idx = lane; idx < count; idx += 64) {
-          const int q = idx % NQ2, el = idx / NQ2;
-          const int i = i0 + el % ni, j = j0 + el / ni;
-          const int qi = q / NQ, qj = q % NQ;
-          double d[3];
-          d[a] = da;
-          d[t0] = i + 0.5 + qd.xq[qj] - xs[t0];
-          d[t1] = j + 0.5 + qd.xq[qi] - xs[t1];
-          const double r2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
-          const double ri = 1.0 / sqrt(r2), ri3 = ri * ri * ri;
-          const double w = lwp[(size_t(j) * n + i) * NQ2 + q];
-          const double nd = sgn * da;
-          const double c5 = 3.0 * nd * ri3 * ri * ri;
-          gx += w * (c5 * d[0] - (a == 0 ? sgn : 0.0) * ri3);
-          gy += w * (c5 * d[1] - (a == 1 ? sgn : 0.0) * ri3);
-          gz += w * (c5 * d[2] - (a == 2 ? sgn : 0.0) * ri3);
-          dq += w * nd * ri3;
+          // point (u, v): element (u / NQ, v / NQ), its point (v % NQ) NQ + u % NQ
+          const int ei = u / NQ, ej = v / NQ;
+          const double w = lwp[(ej * n + ei) * NQ2 + (v - ej * NQ) * NQ + (u - ei * NQ)];
+          const double d0 = ps[t0][u] - xs[t0], d1 = ps[t1][v] - xs[t1];
+          const double ri = rsqrt_pos(fma(d0, d0, fma(d1, d1, da2))), ri2 = ri * ri;
+          const double w3 = w * ri * ri2, w5 = w3 * ri2;
+          s3 += w3;
+          s5 += w5;
+          m0 = fma(w5, d0, m0);
+          m1 = fma(w5, d1, m1);
+          u += du;
+          v += dv;
+          if (u >= len[t0]) {
+            u -= len[t0];
+            ++v;
+          }
         }
+        const double nd = sgn * da, ga = 3.0 * nd * da * s5 - sgn * s3;
+        m0 *= 3.0 * nd;
+        m1 *= 3.0 * nd;
+        if (a == 0) { gx += ga; gy += m0; gz += m1; }
+        else if (a == 1) { gx += m0; gy += ga; gz += m1; }
+        else { gx += m0; gy += m1; gz += ga; }
+        dq += nd * s3;
       }
     }
     wave_sum4(gx, gy, gz, dq);
@@ -931,15 +993,15 @@ int launch_box_flux(hipStream_t s, int nb, int n, int nsr, int p, int64_t N, con
   const size_t P = size_t(p) * n + 1;
   switch (p) {
     case 4:
-      hipLaunchKernelGGL(k_box_flux<4>, dim3(g), dim3(128), 0, s, n, nsr, N, qd, start, sg, sQ, Wneg, tF);
+      hipLaunchKernelGGL(k_box_flux<4>, dim3(g), dim3(256), 0, s, n, nsr, N, qd, start, sg, sQ, Wneg, tF);
       hipLaunchKernelGGL(k_box_flux_add<4>, dim3(grid_of(P * P * P * nb)), dim3(256), 0, s, n, nb, tF, f);
       return 0;
     case 5:
-      hipLaunchKernelGGL(k_box_flux<5>, dim3(g), dim3(128), 0, s, n, nsr, N, qd, start, sg, sQ, Wneg, tF);
+      hipLaunchKernelGGL(k_box_flux<5>, dim3(g), dim3(256), 0, s, n, nsr, N, qd, start, sg, sQ, Wneg, tF);
       hipLaunchKernelGGL(k_box_flux_add<5>, dim3(grid_of(P * P * P * nb)), dim3(256), 0, s, n, nb, tF, f);
       return 0;
     case 6:
-      hipLaunchKernelGGL(k_box_flux<6>, dim3(g), dim3(128), 0, s, n, nsr, N, qd, start, sg, sQ, Wneg, tF);
+      hipLaunchKernelGGL(k_box_flux<6>, dim3(g), dim3(256), 0, s, n, nsr, N, qd, start, sg, sQ, Wneg, tF);
       hipLaunchKernelGGL(k_box_flux_add<6>, dim3(grid_of(P * P * P * nb)), dim3(256), 0, s, n, nb, tF, f);
       return 0;
     default: return -1;
