@@ -8,10 +8,11 @@
 // in LDS (its right side too, except a first level above 18^3, which reads it
 // from global memory), and a step costs one barrier: 31 us per cycle from
 // 16^3 against 76 us of launches, 12 against 38 from 8^3, 50 against 84 from
-// 20^3.  Bound by the LDS reads of the 27-point operator: each thread sums
-// three values per plane (centre, sides, corners of the 3 x 3 square) and
-// reuses them along its run of nodes in z.  Above 20^3 two iterates no longer
-// fit the LDS.
+// 20^3.  Bound by each step's chain of LDS reads, update and barrier: each
+// thread sums three values per plane (centre, sides, corners of the 3 x 3
+// square) and reuses them along its run of nodes in z.  (The iterate and right
+// side held in registers over a level's visit, a fifth fewer LDS reads: 31.4
+// against 30.6 us from 16^3.)  Above 20^3 two iterates no longer fit the LDS.
 #include <algorithm>
 
 #include "kernels.hpp"
