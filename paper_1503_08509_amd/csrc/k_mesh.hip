@@ -454,7 +454,8 @@ __global__ __launch_bounds__(256) void k_cheb_first(LevelOpT<T> op, int K, const
 // ----------------------------------------------------------------- transfers
 
 // Restriction R = P^T as three separable passes on a tile of TE^3 coarse
-// elements.  Along one axis, coarse node (e, j) collects the fine nodes s of
+// elements (a tile may be wider than the mesh: 7 on the 3 elements that 6
+// coarsen to).  Along one axis, coarse node (e, j) collects the fine nodes s of
 // coarse element e with weight w[s][j] and, for the vertex j = 0, those of
 // element e - 1 with weight w[s][PC].  The tile reads the fine nodes of its
 // elements plus one coarse element below.
@@ -508,10 +509,10 @@ __global__ __launch_bounds__(256) void k_restrict(TransferT<T> tr, const T *__re
   const int fx0 = NS * (tx * TE - 1), fy0 = NS * (ty * TE - 1), fz0 = NS * (tz * TE - 1);
   if (tid < NF * NF) {  // pass z: one fine (x, y) column per thread, lanes along x
     const int fx = tid % NF, fy = tid / NF;
-    const int gx = wrapi(fx0 + fx, Pf), gy = wrapi(fy0 + fy, Pf);
+    const int gx = wrap_tile(fx0 + fx, Pf), gy = wrap_tile(fy0 + fy, Pf);
     T v[NF], o[CO];
 #pragma unroll
-    for (int i = 0; i < NF; ++i) v[i] = rf[(size_t(wrapi(fz0 + i, Pf)) * Pf + gy) * Pf + gx];
+    for (int i = 0; i < NF; ++i) v[i] = rf[(size_t(wrap_tile(fz0 + i, Pf)) * Pf + gy) * Pf + gx];
     restrict_col<PC, NS, CO, NF>(tr.w, v, o);
 #pragma unroll
     for (int c = 0; c < CO; ++c) G1[(c * NF + fy) * (NF + 1) + fx] = o[c];
@@ -592,10 +593,10 @@ __global__ __launch_bounds__(256) void k_prolong_add(TransferT<T> tr, const T *_
   }
   if (tid < CI * CI) {  // pass z
     const int cx = tid % CI, cy = tid / CI;
-    const int gx = wrapi(cx0 + cx, Pc), gy = wrapi(cy0 + cy, Pc);
+    const int gx = wrap_tile(cx0 + cx, Pc), gy = wrap_tile(cy0 + cy, Pc);
     T v[CI], o[FO];
 #pragma unroll
-    for (int i = 0; i < CI; ++i) v[i] = ec[(size_t(wrapi(cz0 + i, Pc)) * Pc + gy) * Pc + gx];
+    for (int i = 0; i < CI; ++i) v[i] = ec[(size_t(wrap_tile(cz0 + i, Pc)) * Pc + gy) * Pc + gx];
     prolong_col<PC, NS, CI, FO>(tr.w, v, o);
 #pragma unroll
     for (int f = 0; f < FO; ++f) H1[(f * CI + cy) * (CI + 1) + cx] = o[f];

@@ -1,12 +1,10 @@
 // Device helpers shared by the mesh kernels.
 #pragma once
 
+#include "index_wrap.hpp"
 #include "kernels.hpp"
 
 namespace fep3m {
-
-// Periodic wrap of an index known to lie in [-P, 2P).
-__device__ __forceinline__ int wrapi(int i, int P) { return i < 0 ? i + P : (i >= P ? i - P : i); }
 
 __device__ __forceinline__ double block_sum(double v, double *red) {
   // Fixed-shape tree over the block (deterministic).
