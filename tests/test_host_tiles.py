@@ -55,3 +55,33 @@ def test_transfer_tiles_stay_on_the_mesh(tmp_path, kind):
     body = src[src.index("__global__ __launch_bounds__(256) void k_" + kind):]
     body = body[:body.index("__syncthreads")]
     assert "wrapi(" not in body and body.count("wrap_tile(") == 3   # the columns' three indices go through it
+
+
+def test_march_tiles_stay_on_the_mesh(tmp_path):
+    """Orders 3 to 6, 3 to 512 elements, 1 to 1024 configurations (2^28 elements in all), both kinds of plan: the
+    plan's blocks cover the mesh, and the last input column of the last tile lies below 2 P, where one wrap gives
+    an index of the axis."""
+    code = r"""
+#include "index_wrap.hpp"
+#include "march_plan.hpp"
+#include <cstdio>
+using namespace fep3m;
+int main() {
+  for (int p = 3; p <= 6; ++p)
+    for (int n = 3; n <= 512; ++n)
+      for (int nb = 1; nb <= 1024 && std::int64_t(nb) * n * n * n <= (1 << 28); nb = nb < 8 ? nb + 1 : nb < 1024 ? nb + nb / 8 + 1 > 1024 ? 1024 : nb + nb / 8 + 1 : 1025)
+        for (int shared = 0; shared < 2; ++shared)
+          for (int sys = nb; sys <= 2 * nb; sys += nb) {
+            const MarchPlan q = march_plan(p, n, nb, sys, shared);
+            bool ok = q.nx * q.tx >= n && q.ny * q.ty >= n && q.nz * q.ze >= n && q.blocks() == q.nx * q.ny * q.nz;
+            const int P = p * n, t[2] = {q.tx * q.nx, q.ty * q.ny};
+            for (int k = 0; k < 2; ++k)   // columns -p .. t p of the axis
+              for (int i = -p; i <= t[k] * p; ++i) {
+                const int w = wrapi(i, P);
+                ok = ok && w >= 0 && w < P;
+              }
+            if (!ok) std::printf("p%d_n%d_nb%d_%dx%d ", p, n, nb, q.tx, q.ty);
+          }
+}
+"""
+    assert _run(tmp_path, code) == []
