@@ -5,6 +5,8 @@
 
 #include <cstdint>
 
+#include "rsqrt_step.hpp"
+
 namespace fep3m {
 
 constexpr int kMaxP = 6;           // largest element order handled by the kernels
@@ -85,12 +87,19 @@ __device__ __forceinline__ int xcd_linear(int b, int total) {
 
 // 1 / sqrt(x) for a positive normal x: the hardware estimate refined by one
 // Newton-Raphson step y <- y (3 - x y^2) / 2, written as y + y e / 2 with
-// e = 1 - x y^2 (one step squares the estimate's relative error).
+// e = 1 - x y^2.  The step leaves 1.5 d^2 of the estimate's relative error d:
+// at most 4.2e-15, 3.3e-16 root mean square (measured over 4 million arguments
+// in [1, 4) and in [2e-9, 55]; d is at most 5.2e-8).  For the near pairs of
+// charges, whose arithmetic bounds a call.
 __device__ __forceinline__ double rsqrt_pos(double x) {
   const double y = __builtin_amdgcn_rsq(x);
   const double e = fma(-x * y, y, 1.0);
   return fma(0.5 * y, e, y);
 }
+
+// 1 / sqrt(x) to full length, infinity at 0 and 0 at infinity: at most 1.4e-16
+// over the same arguments (a division by the square root: 1.7e-16).
+__device__ __forceinline__ double rsqrt_full(double x) { return rsqrt_step3(x, __builtin_amdgcn_rsq(x)); }
 
 // Device arrays (nb values each) of the per-configuration PCG scalars.
 struct PcgScalars {

@@ -102,7 +102,7 @@ __global__ __launch_bounds__(256) void k_box_bvals(int n, int nsr, int nb, int64
       for (int i = grp; i < m; i += G) {
         const double4 c = ch[i];
         const double dx = c.x - xb0, dy = c.y - xb1, dz = c.z - xb2;
-        pairs = fma(c.w, rsqrt_pos(fma(dx, dx, fma(dy, dy, dz * dz))), pairs);
+        pairs = fma(c.w, rsqrt_full(fma(dx, dx, fma(dy, dy, dz * dz))), pairs);
       }
     }
   }
@@ -402,7 +402,7 @@ __global__ __launch_bounds__(256) void k_box_charge_bnd(int n, int nsr, int nb, 
         for (int idx = lane; idx < count; idx += 64) {
           const double mval = mf[size_t(u) * st0 + size_t(v) * st1];
           const double d0 = pu[u] - xs[t0], d1 = pv[v] - xs[t1];
-          const double ri = rsqrt_pos(fma(d0, d0, fma(d1, d1, da2)));
+          const double ri = rsqrt_full(fma(d0, d0, fma(d1, d1, da2)));
           const double q = mval * ri, w = q * ri * ri;
           m0 += w;
           mu0 = fma(w, d0, mu0);
@@ -504,7 +504,7 @@ __global__ __launch_bounds__(256) void k_box_flux(int n, int nsr, int64_t N, Box
       for (int k = grp; k < m; k += G) {
         const double4 c = ch[k];
         const double d0 = X[0] - c.x, d1 = X[1] - c.y, d2 = X[2] - c.z;
-        const double ri = rsqrt_pos(fma(d0, d0, fma(d1, d1, d2 * d2)));
+        const double ri = rsqrt_full(fma(d0, d0, fma(d1, d1, d2 * d2)));
         const double da = a == 0 ? d0 : (a == 1 ? d1 : d2);
         dn -= c.w * da * (ri * ri * ri);
       }
@@ -676,7 +676,7 @@ __global__ __launch_bounds__(256) void k_box_flux_charge(int n, int nsr, int nb,
           const int ei = u / NQ, ej = v / NQ;
           const double w = lwp[(ej * n + ei) * NQ2 + (v - ej * NQ) * NQ + (u - ei * NQ)];
           const double d0 = ps[t0][u] - xs[t0], d1 = ps[t1][v] - xs[t1];
-          const double ri = rsqrt_pos(fma(d0, d0, fma(d1, d1, da2))), ri2 = ri * ri;
+          const double ri = rsqrt_full(fma(d0, d0, fma(d1, d1, da2))), ri2 = ri * ri;
           const double w3 = w * ri * ri2, w5 = w3 * ri2;
           s3 += w3;
           s5 += w5;
