@@ -765,10 +765,20 @@ void fep3m_ctx::build_conv() {
     dev_bytes = bytes;
     return;
   }
+  // The spectrum is kept for one octant and takes the rest by reflection, so
+  // the tables must be symmetric to the last bit: what they miss (1e-14 of
+  // their largest value, the rounding of their solves) would pass between the
+  // two channels of a complex one, from node to node with changing sign, where
+  // the forces' derivative picks it up.  T is read by nothing else from here.
+  {
+    Vec Ts = T_host;
+    symmetrise_tables(p, nl, nsr, Ts);
+    hip_check(hipMemcpy(T, Ts.data(), Ts.size() * sizeof(double), hipMemcpyHostToDevice), "upload tables");
+  }
   std::vector<double2> tw(cv.N);
-  for (int j = 0; j < cv.N; ++j) {
-    const double t = 2.0 * M_PI * double(j) / double(cv.N);
-    tw[j] = make_double2(std::cos(t), -std::sin(t));
+  for (int j = 0; j < cv.N; ++j) {   // to the last bit too: an angle rounded to float64 leaves 7e-16
+    const long double t = 2.0L * 3.14159265358979323846264338327950288L * j / cv.N;
+    tw[j] = make_double2(double(std::cos(t)), double(-std::sin(t)));
   }
   hip_check(hipMemcpy(cv.tw, tw.data(), tw.size() * sizeof(double2), hipMemcpyHostToDevice), "upload twiddles");
   launch_conv_spec(stream, cv, T);
