@@ -166,6 +166,13 @@ enum {
                              DIRECT to about 1e-14 relative (Phi, F).           */
 };
 
+/* How the near field and its transpose run (fep3m_stats.near_path). */
+enum {
+  FEP3M_NEAR_PATH_SUMS = 0,     /* the table sums (DIRECT)                         */
+  FEP3M_NEAR_PATH_FFT = 1,      /* FFTs of the power-of-two lattice (FFT)          */
+  FEP3M_NEAR_PATH_LATTICE = 2   /* mixed-radix transforms (AUTO only)              */
+};
+
 typedef struct {
   int32_t n_sr;          /* near block radius in elements (default 3: 7^3 block,
                             the paper's short-range list, Section 4)             */
@@ -241,6 +248,9 @@ typedef struct {
   int32_t near_fft;          /* 1: the near field and its transpose run as FFTs of
                                 the power-of-two lattice (FEP3M_NEAR_FFT's path;
                                 0 with AUTO's mixed-radix transforms too)         */
+  int32_t near_path;         /* FEP3M_NEAR_PATH_*: what near_field came to; AUTO's
+                                choice also depends on the batch and on the memory
+                                that was free at create                           */
   int64_t device_bytes;      /* device memory the context holds                   */
 } fep3m_stats;
 

@@ -34,6 +34,10 @@ NEAR_AUTO = 0
 NEAR_DIRECT = 1
 NEAR_FFT = 2
 
+NEAR_PATH_SUMS = 0
+NEAR_PATH_FFT = 1
+NEAR_PATH_LATTICE = 2
+
 STAGES = {"perm": 0, "start": 1, "C": 2, "b": 3, "phi": 4, "Phi_p": 5, "Phi_m": 6, "T": 7}
 
 
@@ -54,7 +58,7 @@ class Stats(ctypes.Structure):
                 ("pair_item_targets", ctypes.c_int32), ("pair_waves", ctypes.c_int32),
                 ("tune_ms_best", ctypes.c_double), ("tune_ms_default", ctypes.c_double),
                 ("graph_replays", ctypes.c_int64), ("near_fft", ctypes.c_int32),
-                ("device_bytes", ctypes.c_int64)]
+                ("near_path", ctypes.c_int32), ("device_bytes", ctypes.c_int64)]
 
 
 PROF_SLOTS = ["sort", "assign", "solve", "near", "pair", "interp", "fine_apply", "total",

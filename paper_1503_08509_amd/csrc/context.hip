@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <memory>
@@ -25,6 +26,11 @@
 #include "kernels.hpp"
 
 using namespace fep3m;
+
+// near_path takes the place of padding: the layout is that of callers built without it
+static_assert(offsetof(fep3m_stats, near_path) == 100 && offsetof(fep3m_stats, device_bytes) == 104 &&
+                  sizeof(fep3m_stats) == 112,
+              "fep3m_stats layout");
 
 namespace {
 
@@ -598,6 +604,7 @@ void fep3m_ctx::build(double L_, const std::vector<int64_t> &Ns, int n_, int q_,
   if (near_fft) build_near_fft();
   else build_conv();
   stats.near_fft = near_fft ? 1 : 0;
+  stats.near_path = near_fft ? FEP3M_NEAR_PATH_FFT : conv ? FEP3M_NEAR_PATH_LATTICE : FEP3M_NEAR_PATH_SUMS;
   auto t1 = std::chrono::steady_clock::now();
   stats.create_seconds = std::chrono::duration<double>(t1 - t0).count();
   stats.mg_levels = int(lv.size());
