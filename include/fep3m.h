@@ -149,8 +149,12 @@ enum {
                              a little more) is a product of two factors up to
                              11 or 13: the same maps by mixed-radix transforms,
                              any screen family, any boundary.  Else (mixed
-                             precision, larger n, a spectrum above 32 GB or
-                             more than memory holds) DIRECT                      */
+                             precision, larger n, a spectrum above 32 GiB, or
+                             arrays above a quarter of the device memory that is
+                             free at create) DIRECT.  The arrays: 0.6 to 2.6 GB
+                             at n = 64 for the families of up to 27 moments of
+                             order 4, 6.9, 9.1 and 26.6 GB for the one-element
+                             q = 4 and the 27-element q = 3 and 4 screens        */
   FEP3M_NEAR_DIRECT = 1,  /* the table sums themselves: 2 * 8 * (p+1)^3 FLOP per
                              element and near offset (matrix cores forward,
                              vector units for the transpose)                    */

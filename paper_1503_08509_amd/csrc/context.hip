@@ -293,17 +293,18 @@ struct fep3m_ctx {
   template <class T>
   T *alloc(size_t count, const char *what) {
     const size_t bytes = count * sizeof(T) + 64;
-    dev_bytes += bytes;
     if (arena) {
       const size_t at = (arena_used + 255) & ~size_t(255);
       if (at + bytes > kStaticBytes)
         throw Status(FEP3M_ERR_ARG, std::string("static storage of ") + std::to_string(kStaticBytes >> 20) +
                                         " MiB exceeded at " + what + " (the context needs more; use fep3m_create_ex)");
       arena_used = at + bytes;
+      dev_bytes += bytes;
       return reinterpret_cast<T *>(arena + at);
     }
     T *p = dalloc<T>(count, what);
     allocs.push_back(p);
+    dev_bytes += bytes;
     return p;
   }
   // host mirror of `count` doubles: pinned, or ordinary memory for static contexts
@@ -742,35 +743,36 @@ void fep3m_ctx::build_mg() {
 
 // The convolution's plan, spectrum and work arrays, where near_field = AUTO
 // leaves the choice, in float64 (the table sums of mixed precision are
-// float32).  The table sums stay where the lattice has no plan, where the
-// spectrum would exceed kConvSpecMax, and where its memory is not to be had.
-// At 64^3 the 27-element q = 4 screens' takes 25 GB (399 ms per call with 10^6
-// charges by the table sums, 127 so), every other family's less than 8.
-constexpr size_t kConvSpecMax = size_t(32) << 30;
+// float32).  The table sums stay where the lattice has no plan and where its
+// memory is not to be had (conv_rules.hpp).
 void fep3m_ctx::build_conv() {
   if (mixed || opt.near_field != FEP3M_NEAR_AUTO || !conv_plan(n, nsr, p, nl, box, cv)) return;
   const size_t N3 = size_t(cv.N) * cv.N * cv.N * nb, cc = (cv.na + 1) / 2, cm = (cv.M + 1) / 2;
-  const size_t ns = conv_spec_size(cv);
-  if (ns * sizeof(double2) > kConvSpecMax) return;
-  const size_t want = (ns + N3 * 2 * (cc + cm) + cv.N) * sizeof(double2) + 6 * 512;
-  // static storage also keeps room for the staging buffers of graph mode
-  const size_t staging = opt.use_graph ? (9 * size_t(N) + nb) * sizeof(double) + 6 * 512 : 0;
-  if (arena && arena_used + want + staging > kStaticBytes) return;
-  const size_t held = allocs.size(), bytes = dev_bytes;
+  const size_t ns = conv_spec_values(cv.N, cv.na, cv.M);
+  // one allocation, so that nothing is left behind where it fails
+  auto padded = [](size_t values) { return (values + 15) & ~size_t(15); };
+  const size_t sizes[6] = {padded(cv.N), padded(ns), padded(N3 * cc), padded(N3 * cc), padded(N3 * cm), padded(N3 * cm)};
+  size_t all = 0;
+  for (size_t v : sizes) all += v;
+  if (arena) {
+    if (arena_used + all * sizeof(double2) + 512 > kStaticBytes) return;
+  } else {
+    size_t free_bytes = 0, total = 0;
+    hip_check(hipMemGetInfo(&free_bytes, &total), "free memory");
+    if (!conv_memory(ns * sizeof(double2), all * sizeof(double2), free_bytes)) return;
+  }
+  double2 *at = nullptr;
   try {
-    cv.tw = alloc<double2>(size_t(cv.N), "lattice twiddles");
-    cv.S = alloc<double2>(ns, "table spectrum");
-    cv.zc = alloc<double2>(N3 * cc, "transformed moments");
-    cv.za = alloc<double2>(N3 * cc, "transformed moment adjoint");
-    cv.zpsi = alloc<double2>(N3 * cm, "transformed near-screen field");
-    cv.zg = alloc<double2>(N3 * cm, "transformed deposits");
-  } catch (const Status &e) {
+    at = alloc<double2>(all, "transforms of the near field");
+  } catch (const Status &e) {   // taken by another since
     if (e.code != FEP3M_ERR_OOM) throw;
     (void)hipGetLastError();
-    for (size_t i = held; i < allocs.size(); ++i) (void)hipFree(allocs[i]);
-    allocs.resize(held);
-    dev_bytes = bytes;
     return;
+  }
+  double2 **arrays[6] = {&cv.tw, &cv.S, &cv.zc, &cv.za, &cv.zpsi, &cv.zg};
+  for (int k = 0; k < 6; ++k) {
+    *arrays[k] = at;
+    at += sizes[k];
   }
   // The spectrum is kept for one octant and takes the rest by reflection, so
   // the tables must be symmetric to the last bit: what they miss (1e-14 of

@@ -452,18 +452,6 @@ __global__ __launch_bounds__(256) void k_conv_prod(ConvProd a) {
   }
 }
 
-bool radices(int N, int &r1, int &r2) {
-  for (int d = 1; d <= 13; ++d) {   // the split nearest to square, the larger factor first
-    if (d == 12 || N % d) continue;
-    const int e = N / d;
-    if (e > 13 || e == 12) continue;
-    r1 = d;
-    r2 = e;
-    if (d >= e) return true;
-  }
-  return r1 > 0;
-}
-
 template <int IN, int OUT>
 void pass(hipStream_t s, const ConvPass &a) {
   const size_t total = size_t(a.nb) * a.e1 * a.e2 * a.CH;
@@ -534,23 +522,15 @@ void inverse(hipStream_t s, const ConvPlan &c, int nb, int nch, double2 *z, doub
 
 bool conv_plan(int n, int nsr, int p, int nl, bool box, ConvPlan &c) {
   c = ConvPlan{};
-  if (n > 64) return false;
   c.n = n;
-  c.N = box ? n + nsr : n;
+  c.N = conv_edge(n, nsr, box);
   c.nsr = nsr;
   c.p = p;
   c.nl = nl;
   c.na = nl * nl * nl;
   c.M = (p + 1) * (p + 1) * (p + 1);
   c.box = box;
-  if (!box) return radices(c.N, c.r1, c.r2);
-  while (!radices(c.N, c.r1, c.r2)) ++c.N;   // padded: the next edge with two radices
-  return true;
-}
-
-size_t conv_spec_size(const ConvPlan &c) {
-  const size_t H = c.N / 2 + 1;
-  return H * H * H * c.na * c.M;
+  return c.N > 0 && radices(c.N, c.r1, c.r2);
 }
 
 void launch_conv_spec(hipStream_t s, const ConvPlan &c, const double *T) {

@@ -1,6 +1,7 @@
 // Host launchers of the gfx950 kernels (one declaration per launcher).
 #pragma once
 
+#include "conv_rules.hpp"
 #include "device_common.hpp"
 
 namespace fep3m {
@@ -209,10 +210,9 @@ int launch_adj_lambda(hipStream_t s, int nb, int n, int p, const double *lam, co
 
 // near field and its transpose by transforms of a lattice of any edge
 // N = r1 r2 (factors up to 11 and 13), every screen family, periodic or box
-// (k_conv.hip), float64.  S: conv_spec_size complex values; tw:
+// (k_conv.hip), float64.  S: conv_spec_values complex values; tw:
 // exp(-2 pi i j / N); work arrays of nb N^3 complex channels: zc, za
 // ceil(na / 2), zpsi, zg ceil(M / 2).
-constexpr int kConvMaxN = 72;
 struct ConvPlan {
   int n, N, r1, r2, nsr, p, nl, na, M;
   bool box;
@@ -220,7 +220,6 @@ struct ConvPlan {
 };
 // false: no plan (n above 64, or a factor above 13)
 bool conv_plan(int n, int nsr, int p, int nl, bool box, ConvPlan &c);
-size_t conv_spec_size(const ConvPlan &c);
 void launch_conv_spec(hipStream_t s, const ConvPlan &c, const double *T);
 // transforms of the moments and / or the deposits, and the products
 void launch_conv_products(hipStream_t s, const ConvPlan &c, int nb, const double *C, const double *gE);
