@@ -149,7 +149,8 @@ enum {
                              a little more) is a product of two factors up to
                              11 or 13: the same maps by mixed-radix transforms,
                              any screen family, any boundary.  Else (mixed
-                             precision, larger n, a spectrum above 32 GiB, or
+                             precision, larger n, n_sr = 1 on large meshes and
+                             batches where DIRECT is faster, a spectrum above 32 GiB, or
                              arrays above a quarter of the device memory that is
                              free at create) DIRECT.  The arrays: 0.6 to 2.6 GB
                              at n = 64 for the families of up to 27 moments of

@@ -743,10 +743,11 @@ void fep3m_ctx::build_mg() {
 
 // The convolution's plan, spectrum and work arrays, where near_field = AUTO
 // leaves the choice, in float64 (the table sums of mixed precision are
-// float32).  The table sums stay where the lattice has no plan and where its
-// memory is not to be had (conv_rules.hpp).
+// float32).  The table sums stay where the lattice has no plan, where they are
+// the faster path and where the memory is not to be had (conv_rules.hpp).
 void fep3m_ctx::build_conv() {
   if (mixed || opt.near_field != FEP3M_NEAR_AUTO || !conv_plan(n, nsr, p, nl, box, cv)) return;
+  if (!conv_pays(n, cv.N, nsr, p, nl, box, nb)) return;
   const size_t N3 = size_t(cv.N) * cv.N * cv.N * nb, cc = (cv.na + 1) / 2, cm = (cv.M + 1) / 2;
   const size_t ns = conv_spec_values(cv.N, cv.na, cv.M);
   // one allocation, so that nothing is left behind where it fails

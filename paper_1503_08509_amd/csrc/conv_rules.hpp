@@ -56,4 +56,32 @@ constexpr bool conv_memory(size_t spectrum, size_t bytes, size_t free_bytes) {
   return spectrum <= kConvSpecMax && bytes <= free_bytes / 4;
 }
 
+// Whether the transforms are the faster path, for nl moments per axis at order
+// p.  With n_sr = 3 they are for every mesh, family and batch (at least 1.3
+// times; 343 offsets per element against a few radix steps).  With n_sr = 1
+// the table sums have 27 offsets, and on a chip that a large lattice or batch
+// fills they win: near field and moment adjoint of the transforms and the sums,
+// in ms, on 65536 elements as 16 configurations of 16^3: 27-element q = 1 0.29
+// and 0.16, one-element q = 4 2.72 and 1.87, 27-element q = 4 14.3 and 7.0, a
+// box (one-element q = 3) 1.06 and 0.52; on one 16^3 mesh 0.088 and 0.109, 0.29
+// and 1.07, 1.14 and 3.86, 0.16 and 0.34.  The line is drawn in elements, per
+// family at its crossing (8000 to 14000; 20000 to 33000; 64000 and 110000 to
+// 125000): an element counts by the lattice it is padded to, squared, since the products'
+// octants and the passes both grow with it, and from 27 moments on, where the
+// sums are bound by arithmetic, by the share of their bricks of 4 x 4 x 8
+// elements that the mesh fills (27-element q = 3, 1000 configurations of 5^3: 5.3
+// and 13.6 ms).  With n_sr = 2 the sums win only in large batches of boxes whose
+// bricks are full and whose lattice holds twice the elements (8^3 on 10^3, one-
+// element q = 3, 256 configurations: 3.7 and 2.9 ms; 16 of them 0.29 and 0.98).
+constexpr bool conv_pays(int n, int N, int nsr, int p, int nl, bool box, int nb) {
+  const double el = double(n) * n * n, lattice = double(N) * N * N, pad = lattice / el;
+  if (nsr == 1) {
+    const int u = (n + 3) / 4 * 4, v = (n + 7) / 8 * 8;
+    const double bricks = nl >= 3 ? double(u) * u * v / el : 1.0;
+    const double line = nl == 1 ? 115000.0 : p == 3 ? 8192.0 : p == 4 || (p == 5 && nl > 2) ? 64000.0 : 20000.0;
+    return nb * lattice * pad <= line * bricks;
+  }
+  return !(nsr == 2 && box && nl == 2 && n % 8 == 0 && pad > 1.9 && nb * lattice > 1e5);
+}
+
 }  // namespace fep3m

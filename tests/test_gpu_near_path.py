@@ -44,3 +44,20 @@ def test_static_storage_without_room_for_the_transforms():
         return p
     assert path(20) == fp.NEAR_PATH_SUMS
     assert path(9) == fp.NEAR_PATH_LATTICE
+
+
+@pytest.mark.parametrize("n,nb,path", [(16, 4, "LATTICE"), (16, 16, "SUMS")])
+def test_batches_of_the_smallest_block(n, nb, path):
+    """n_sr = 1: the table sums above 20000 elements in all (one-element q = 4), by transforms or sums the same result."""
+    torch = pytest.importorskip("torch")
+    import numpy as np
+
+    rng = np.random.default_rng(nb)
+    c, kw = 20, dict(q=4, n_sr=1, solver=fp.SOLVER_FDM)
+    x = torch.from_numpy(rng.random((c * nb, 3))).cuda()
+    Q = torch.from_numpy(np.tile(np.repeat([1.0, -1.0], c // 2), nb)).cuda()
+    a, b = fp.Context(1.0, [c] * nb, n, **kw), fp.Context(1.0, [c] * nb, n, near_field=fp.NEAR_DIRECT, **kw)
+    assert a.stats()["near_path"] == getattr(fp, "NEAR_PATH_" + path)
+    oa, ob = (v.energy_forces(x, Q, dUdQ=True, Phi=True) for v in (a, b))
+    for k in ("Phi", "F", "dUdQ"):
+        assert float((oa[k] - ob[k]).norm() / ob[k].norm()) < conv.TOL
