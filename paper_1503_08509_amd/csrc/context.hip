@@ -255,11 +255,10 @@ struct fep3m_ctx {
   // Default priority, like every stream here.
   hipStream_t pstream = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-  hipEvent_t ev_copied = nullptr;   // after a copy to the host that is read while later work runs
-  void mark_copied() {
-    if (!ev_copied) hip_check(hipEventCreateWithFlags(&ev_copied, hipEventDisableTiming), "event");
-    hip_check(hipEventRecord(ev_copied, stream), "event");
-  }
+  // after a copy to the host that is read while later work runs; made at
+  // create, as calls on a static context make nothing
+  hipEvent_t ev_copied = nullptr;
+  void mark_copied() { hip_check(hipEventRecord(ev_copied, stream), "event"); }
   void wait_copied(const char *what) { hip_check(hipEventSynchronize(ev_copied), what); }
   void side_stream() {   // created before any capture begins
     if (pstream) return;
@@ -589,6 +588,7 @@ void fep3m_ctx::build(double L_, const std::vector<int64_t> &Ns, int n_, int q_,
   partial_len = size_t(4 * kRedBlocks) + 64;
   scal = alloc<double>(64, "scalars");
   host_scal = host_mirror(64, host_scal_buf, "pinned scalars");
+  hip_check(hipEventCreateWithFlags(&ev_copied, hipEventDisableTiming), "event");
 
   build_mg();
   if (box) build_box();
