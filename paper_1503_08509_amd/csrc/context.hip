@@ -478,7 +478,7 @@ void fep3m_ctx::build(double L_, const std::vector<int64_t> &Ns, int n_, int q_,
   generic = !(o.support == FEP3M_SUPPORT_ONE && q == 3);
   box = o.boundary != FEP3M_BOUNDARY_PERIODIC;
   insulated = o.boundary == FEP3M_BOUNDARY_INSULATED;
-  if (box) {   // the box runs on the float64 table-sum kernels, the pair sum on rows of elements
+  if (box) {   // the box runs on the families' float64 kernels, the pair sum on rows of elements
     generic = true;
     plan = PairPlan{2, 2, 0};
     tuned = true;
@@ -2084,9 +2084,9 @@ int create_common(double L, const std::vector<int64_t> &Ns, const int32_t dims[3
     g_create_error = "element orders above 6 (one-element screens of degree 5 and 6) are not implemented";
     return FEP3M_ERR_UNSUPPORTED;
   }
-  if (!(o.support == FEP3M_SUPPORT_ONE && q == 3)) {   // the other screen families: float64, table sums
+  if (!(o.support == FEP3M_SUPPORT_ONE && q == 3)) {   // the other screen families: float64
     if (o.precision != FEP3M_PRECISION_FP64 || o.near_field == FEP3M_NEAR_FFT) {
-      g_create_error = "screens other than the one-element q = 3 screen run in float64 with the direct near field";
+      g_create_error = "screens other than the one-element q = 3 screen run in float64 with near_field = AUTO or DIRECT";
       return FEP3M_ERR_UNSUPPORTED;
     }
   }
@@ -2095,7 +2095,7 @@ int create_common(double L, const std::vector<int64_t> &Ns, const int32_t dims[3
       (o.support != FEP3M_SUPPORT_ONE || o.precision != FEP3M_PRECISION_FP64 || o.solver != FEP3M_SOLVER_FDM ||
        o.near_field == FEP3M_NEAR_FFT || o.use_graph || static_storage)) {
     g_create_error = "the grounded and insulating boxes take one-element screens in float64 with the exact mesh solve "
-                     "and the direct near field, eager (no graph, no static storage)";
+                     "and near_field = AUTO or DIRECT, eager (no graph, no static storage)";
     return FEP3M_ERR_UNSUPPORTED;
   }
   int dev = -1;
