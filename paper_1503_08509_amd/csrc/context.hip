@@ -775,23 +775,13 @@ void fep3m_ctx::build_conv() {
     *arrays[k] = at;
     at += sizes[k];
   }
-  // The spectrum is kept for one octant and takes the rest by reflection, so
-  // the tables must be symmetric to the last bit: what they miss (1e-14 of
-  // their largest value, the rounding of their solves) would pass between the
-  // two channels of a complex one, from node to node with changing sign, where
-  // the forces' derivative picks it up.  T is read by nothing else from here.
-  {
-    Vec Ts = T_host;
-    symmetrise_tables(p, nl, nsr, Ts);
-    hip_check(hipMemcpy(T, Ts.data(), Ts.size() * sizeof(double), hipMemcpyHostToDevice), "upload tables");
-  }
   std::vector<double2> tw(cv.N);
-  for (int j = 0; j < cv.N; ++j) {   // to the last bit too: an angle rounded to float64 leaves 7e-16
+  for (int j = 0; j < cv.N; ++j) {   // to the last bit: an angle rounded to float64 leaves 7e-16
     const long double t = 2.0L * 3.14159265358979323846264338327950288L * j / cv.N;
     tw[j] = make_double2(double(std::cos(t)), double(-std::sin(t)));
   }
   hip_check(hipMemcpy(cv.tw, tw.data(), tw.size() * sizeof(double2), hipMemcpyHostToDevice), "upload twiddles");
-  launch_conv_spec(stream, cv, T);
+  launch_conv_spec(stream, cv, T);   // T is read by nothing else from here
   check_launch("table spectrum");
   hip_check(hipStreamSynchronize(stream), "table spectrum");
   conv = true;
@@ -1234,7 +1224,7 @@ void fep3m_ctx::box_apply(const double *v, double *y) {
 // zero_boundary: sol is zero on the boundary too (K_IB phi_B = 0, no apply).
 void fep3m_ctx::box_solve(const double *rhs, double *sol, int which, bool zero_boundary) {
   const int Pi = Pb - 2;
-  const size_t nv = size_t(Pb) * Pb * Pb * nb, ni = size_t(Pi) * Pi * Pi * nb;
+  const size_t nv = size_t(Pb) * Pb * Pb * nb;
   int K;
   if (zero_boundary) {
     K = launch_box_resid(stream, Pb, nb, true, false, rhs, nullptr, partial);

@@ -290,28 +290,4 @@ void compute_tables(int p, const Screen1D &scr, int n_sr, int B, Vec &T) {
   });
 }
 
-void symmetrise_tables(int p, int nl, int n_sr, Vec &T) {
-  const int q1 = p + 1, S = 2 * n_sr + 1;
-  const size_t M = size_t(q1) * q1 * q1, ND = size_t(S) * S * S, na = size_t(nl) * nl * nl;
-  for (int ax = 0; ax < 3; ++ax) {   // an axis averaged last leaves the others' symmetry as it is
-    const size_t sa = ax == 0 ? 1 : ax == 1 ? nl : size_t(nl) * nl;
-    const size_t sD = ax == 0 ? 1 : ax == 1 ? S : size_t(S) * S, sm = ax == 0 ? 1 : ax == 1 ? q1 : size_t(q1) * q1;
-    for (size_t a = 0; a < na; ++a) {
-      const double sg = (a / sa % nl) % 2 ? -1.0 : 1.0;
-      for (size_t D = 0; D < ND; ++D) {
-        const size_t k = D / sD % S, Dr = D + (S - 1 - 2 * k) * sD;
-        if (Dr < D) continue;
-        for (size_t m = 0; m < M; ++m) {
-          const size_t j = m / sm % q1, mr = m + (q1 - 1 - 2 * j) * sm;
-          if (Dr == D && mr < m) continue;
-          double &u = T[(a * ND + D) * M + m], &v = T[(a * ND + Dr) * M + mr];
-          const double t = 0.5 * (u + sg * v);
-          u = t;
-          v = sg * t;
-        }
-      }
-    }
-  }
-}
-
 }  // namespace fep3m

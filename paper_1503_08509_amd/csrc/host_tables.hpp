@@ -11,9 +11,4 @@ namespace fep3m {
 // in elements (odd, > 2 n_sr + 1).
 void compute_tables(int p, const Screen1D &scr, int n_sr, int B, Vec &T);
 
-// The tables averaged over the axis reflections, under which they are
-// symmetric (offset, node and the sign of odd powers) but for the rounding of
-// the solves: exactly symmetric afterwards.
-void symmetrise_tables(int p, int nl, int n_sr, Vec &T);
-
 }  // namespace fep3m

@@ -22,6 +22,7 @@
 // (q = 3), 2.8 ms in a grounded box of 32^3, 4.9 ms for the 27-element q = 2
 // screen at n = 24; here 0.29, 0.42 and 0.22 ms.
 #include "kernels.hpp"
+#include "table_symmetry.hpp"
 
 namespace fep3m {
 
@@ -257,6 +258,16 @@ __global__ __launch_bounds__(256) void k_conv_pass(ConvPass a) {
       FEP3M_RADIX_SWITCH(a.r2, CALL)
 #undef CALL
     }
+}
+
+// The spectrum is kept for one octant and takes the rest by reflection, so the
+// tables behind it must be symmetric to the last bit: what they miss (1e-14 of
+// their largest value) would pass between the two channels of a complex one,
+// from node to node with changing sign, where the forces' derivative picks it
+// up (an error of 1.4e-13 instead of 1.8e-14: one-element q = 2, 9^3).
+__global__ __launch_bounds__(256) void k_conv_symmetrise(size_t count, int p, int nl, int nsr, double *T) {
+  const size_t i = size_t(blockIdx.x) * 256 + threadIdx.x;
+  if (i < count) symmetrise_entry(i, p, nl, nsr, T);
 }
 
 // Spectrum at 8 octant frequencies per block and one moment (blockIdx.y).
@@ -533,7 +544,10 @@ bool conv_plan(int n, int nsr, int p, int nl, bool box, ConvPlan &c) {
   return c.N > 0 && radices(c.N, c.r1, c.r2);
 }
 
-void launch_conv_spec(hipStream_t s, const ConvPlan &c, const double *T) {
+void launch_conv_spec(hipStream_t s, const ConvPlan &c, double *T) {
+  const int S = 2 * c.nsr + 1;
+  const size_t count = size_t(c.na) * S * S * S * c.M;
+  hipLaunchKernelGGL(k_conv_symmetrise, dim3(unsigned((count + 255) / 256)), dim3(256), 0, s, count, c.p, c.nl, c.nsr, T);
   const int H = c.N / 2 + 1, NO = H * H * H;
   hipLaunchKernelGGL(k_conv_spec, dim3((NO + 7) / 8, c.na), dim3(256), 0, s, c.N, NO, c.nsr, c.na, c.M, T, c.tw, c.S);
 }

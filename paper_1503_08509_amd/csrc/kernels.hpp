@@ -220,7 +220,8 @@ struct ConvPlan {
 };
 // false: no plan (n above 64, or a factor above 13)
 bool conv_plan(int n, int nsr, int p, int nl, bool box, ConvPlan &c);
-void launch_conv_spec(hipStream_t s, const ConvPlan &c, const double *T);
+// T is made exactly symmetric under the axis reflections first
+void launch_conv_spec(hipStream_t s, const ConvPlan &c, double *T);
 // transforms of the moments and / or the deposits, and the products
 void launch_conv_products(hipStream_t s, const ConvPlan &c, int nb, const double *C, const double *gE);
 // W = phi - Psi (null phi: -Psi) from the products; sign * B into A [E][na]

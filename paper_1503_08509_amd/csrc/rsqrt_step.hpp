@@ -1,11 +1,7 @@
 // Refinement of a reciprocal square root estimate (host and device).
 #pragma once
 
-#ifdef __HIPCC__
-#define FEP3M_HOST_DEVICE __host__ __device__
-#else
-#define FEP3M_HOST_DEVICE
-#endif
+#include "host_device.hpp"
 
 namespace fep3m {
 
