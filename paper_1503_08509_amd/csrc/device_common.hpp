@@ -109,7 +109,6 @@ struct PcgScalars {
 enum PcgStep : int { kPcgStart = 0, kPcgAlpha = 1, kPcgResid = 2, kPcgBeta = 3, kPcgBetaPR = 4 };
 
 enum ApplyMode : int {
-  kApply = 0,      // out = K x
   kResidual = 1,   // out = f - K x
   kCheb = 2,       // xo = x + c1 (x - xprev) + c2 D^-1 (f - K x)   (xo may alias xprev)
   kApplyDot = 3,   // out = K x, block partial of x . (K x)

@@ -573,12 +573,6 @@ __global__ __launch_bounds__(512) void k_parity_transform(int P, int axis, int n
   }
 }
 
-inline int grid_of(size_t count) {
-  size_t g = (count + 255) / 256;
-  if (g < 1) g = 1;
-  return int(g > 65536 ? 65536 : g);
-}
-
 template <int PO>
 int fs_solve_impl(hipStream_t s, int nsys, int n, const double *rhs, double *out, double2 *Z, const double2 *tw,
                   const double2 *W, const double *lam) {

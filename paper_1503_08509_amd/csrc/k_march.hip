@@ -197,7 +197,7 @@ __global__ __launch_bounds__(NT, WPS) void k_apply_march(MarchOp<T, PO> op, Marc
   constexpr bool norm = MODE == kResidualNorm;
   constexpr bool need_f = MODE == kResidual || norm || rr || cheb || zstart || MODE == kChebZ3;
   constexpr bool need_x = cheb || MODE == kChebZ3 || MODE == kApplyDot;
-  constexpr bool need_id = MODE != kApply && MODE != kApplyDot && MODE != kResidual && !norm && !rr;
+  constexpr bool need_id = MODE != kApplyDot && MODE != kResidual && !norm && !rr;
   __shared__ T AB[2 * PO * S::SA];
   __shared__ T Xo[need_x || rr ? S::OWN : 1];   // x (rr: the residual) on the owned nodes
   __shared__ T invd[PO * PO * PO];
@@ -504,7 +504,7 @@ __global__ __launch_bounds__(NT, WPS) void k_apply_march(MarchOp<T, PO> op, Marc
       if (band && zstart) asm volatile("" : "+v"(xv));   // rounded here, as the z pass's input was
       const T rr = (pf_f[r] - y) * id;
       T v;
-      if (MODE == kApply || MODE == kApplyDot) v = y;
+      if (MODE == kApplyDot) v = y;
       else if (MODE == kResidual || norm) v = pf_f[r] - y;
       else if (need_d) v = xv + c1 * (xv - pf_d[r]) + c2 * rr;
       else if (cheb || zstart) v = xv + c1 * xv + c2 * rr;
@@ -604,14 +604,19 @@ int march_impl(hipStream_t s, int nsys, const MarchPlan &pl, const LevelOpT<T> &
     FEP3M_MARCH(kResidual);
     FEP3M_MARCH(kCheb);
     FEP3M_MARCH(kChebFirst);
-    FEP3M_MARCH(kApplyDot);
-    FEP3M_MARCH(kDinvApply);
     FEP3M_MARCH(kChebZ2);
     FEP3M_MARCH(kChebZ3);
-    FEP3M_MARCH(kChebDot);
-    case kResidualNorm:
+    case kApplyDot:
+    case kDinvApply:
+    case kChebDot:
+    case kResidualNorm:   // the float32 cycle has none of these
       if constexpr (sizeof(T) == 8) {
-        switch (mode) { FEP3M_MARCH(kResidualNorm); }
+        switch (mode) {
+          FEP3M_MARCH(kApplyDot);
+          FEP3M_MARCH(kDinvApply);
+          FEP3M_MARCH(kChebDot);
+          FEP3M_MARCH(kResidualNorm);
+        }
         break;
       } else {
         return -1;

@@ -413,7 +413,7 @@ __global__ __launch_bounds__(NT) void k_apply(LevelOpT<T> op, const T *__restric
     const T xv = Xo[lc];
     const T rr = (pf_f[r] - y) * id;
     T v;
-    if (mode == kApply || mode == kApplyDot) v = y;
+    if (mode == kApplyDot) v = y;
     else if (mode == kResidual) v = pf_f[r] - y;
     else if (cheb || zstart) v = xv + c1 * (xv - pf_d[r]) + c2 * rr;
     else if (mode == kChebZ3) v = xv + c1 * (xv - s0 * id * pf_f[r]) + c2 * rr;

@@ -498,14 +498,15 @@ __global__ __launch_bounds__(256) void k_unpermute(int64_t N, double scale, cons
 }
 
 // Ordered near pairs: sum_E count_E * (sum over the block of counts) - N.
-// Eight lanes per element, lane k its block's layer k - NSR (NSR 4: lane 0
-// the last one too); a row of elements is one or two runs of sorted charges.
+// Eight lanes per element, lane k its block's layer k - NSR (n_sr <= 3); a row
+// of elements is one or two runs of sorted charges.
 // One atomic per block and at most 512 blocks: they queue on one address, 13
 // ns each.  14 us on 16^3 elements and 88 on 64^3 with one thread per
 // element, 5 and 60 so.
 template <int NSR>
 __global__ __launch_bounds__(256) void k_pair_count(int n, int MT, const int *__restrict__ start,
                                                     unsigned long long *__restrict__ out) {
+  static_assert(2 * NSR + 1 <= 8, "one lane per layer");
   const int M = n * n * n, k = threadIdx.x & 7;
   unsigned long long tot = 0;
   for (int E = blockIdx.x * 32 + (threadIdx.x >> 3); E < MT; E += gridDim.x * 32) {
@@ -514,16 +515,15 @@ __global__ __launch_bounds__(256) void k_pair_count(int n, int MT, const int *__
     const int ex = El % n, ey = (El / n) % n, ez = El / (n * n);
     const int lo = ex - NSR, hi = ex + NSR;
     long long s = 0;
-    if (c != 0)
-      for (int l = k; l <= 2 * NSR; l += 8) {
-        const int z = (ez + l - NSR + n) % n;
-        for (int dy = -NSR; dy <= NSR; ++dy) {
-          const int *row = start + base + n * ((ey + dy + n) % n + n * z);
-          if (lo < 0) s += (row[n] - row[lo + n]) + (row[hi + 1] - row[0]);
-          else if (hi >= n) s += (row[n] - row[lo]) + (row[hi - n + 1] - row[0]);
-          else s += row[hi + 1] - row[lo];
-        }
+    if (c != 0 && k <= 2 * NSR) {
+      const int z = (ez + k - NSR + n) % n;
+      for (int dy = -NSR; dy <= NSR; ++dy) {
+        const int *row = start + base + n * ((ey + dy + n) % n + n * z);
+        if (lo < 0) s += (row[n] - row[lo + n]) + (row[hi + 1] - row[0]);
+        else if (hi >= n) s += (row[n] - row[lo]) + (row[hi - n + 1] - row[0]);
+        else s += row[hi + 1] - row[lo];
       }
+    }
     tot += (unsigned long long)(c * s - (k == 0 ? c : 0));
   }
   __shared__ unsigned long long wave[4];
@@ -630,7 +630,6 @@ int launch_pair_count(hipStream_t s, int nb, int n, int nsr, const int *start, u
     case 1: hipLaunchKernelGGL(k_pair_count<1>, dim3(grid_n(int64_t(MT) * 8, 512)), dim3(256), 0, s, n, MT, start, out); return 0;
     case 2: hipLaunchKernelGGL(k_pair_count<2>, dim3(grid_n(int64_t(MT) * 8, 512)), dim3(256), 0, s, n, MT, start, out); return 0;
     case 3: hipLaunchKernelGGL(k_pair_count<3>, dim3(grid_n(int64_t(MT) * 8, 512)), dim3(256), 0, s, n, MT, start, out); return 0;
-    case 4: hipLaunchKernelGGL(k_pair_count<4>, dim3(grid_n(int64_t(MT) * 8, 512)), dim3(256), 0, s, n, MT, start, out); return 0;
     default: return -1;
   }
 }
