@@ -10,7 +10,9 @@ interactions/s of the whole step, the step time (the N = 1e6 energy+force
 time on the default workload), the
 roofline position of the dominant kernel (device time from hipEvents the
 library records on its stream), and the FP64 oracle's throughput on a
-bounded sample of the same workload, timed on this host's cores.
+bounded sample of the same workload, timed on this host's cores.  The line
+holds the headline and one figure per further measurement (a record of the
+last few kilobytes of output keeps it whole); --record writes everything.
 """
 from __future__ import annotations
 
@@ -61,6 +63,7 @@ def parse():
                          "1..4 (one-q3 is the method's default; the others skip the variants and the CPU baseline)")
     ap.add_argument("--n-sr", type=int, choices=[1, 2, 3], default=3, help="near block radius (block of 2 n_sr + 1 "
                     "elements per axis)")
+    ap.add_argument("--record", metavar="PATH", help="write the full record (every kernel, variant and sweep row) as JSON")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--no-variants", action="store_true",
                     help="skip the mixed-precision, clustered and batched measurements reported beside the FP64 line")
@@ -285,7 +288,7 @@ def stream_copy_gbs():
     return 2 * 2**30 / (best * 1e-3) / 1e9
 
 
-def kernel_rooflines(prof, steps, mixed, near_fft=False, p=5, moments=8, default_screen=True):
+def kernel_rooflines(prof, steps, mixed, near_path=0, p=5, moments=8, default_screen=True):
     def kern(slot, bound):
         s = prof[slot]
         if s["count"] == 0 or s["ms"] <= 0:
@@ -304,11 +307,16 @@ def kernel_rooflines(prof, steps, mixed, near_fft=False, p=5, moments=8, default
                 "frac": ach / peak, "traffic": None,
                 "avg_launch_ms": s["ms"] / s["count"], "launches_per_step": s["count"] / steps}
 
-    if near_fft:   # transforms and spectrum products: bytes in and out of each launch
+    if near_path == 1:   # transforms and spectrum products: bytes in and out of each launch
         kernels = {"near-screen field (FFTs + spectrum product)": kern("near", "hbm"),
                    "k_pair (near-pair sum)": kern("pair", "alu"),
                    "k_apply p=5 (fine-level operator)": kern("fine_apply", "hbm"),
                    "transposed near field (FFTs + spectrum product)": kern("adj_near", "hbm")}
+    elif near_path == 2:   # operations of the transforms and products that ran
+        kernels = {"near-screen field (mixed-radix transforms)": kern("near", "alu"),
+                   "k_pair (near-pair sum)": kern("pair", "alu"),
+                   f"k_apply p={p} (fine-level operator)": kern("fine_apply", "hbm"),
+                   "transposed near field (mixed-radix transforms)": kern("adj_near", "alu")}
     elif default_screen:
         kernels = {"k_psi (near-screen field)": kern("near", "mfma"),
                    "k_pair (near-pair sum)": kern("pair", "alu"),
@@ -369,7 +377,7 @@ def measure(name, precision, steps, warmup, forces=True, graph=False, solver=0, 
     res = {
         "workload": label, "precision": precision, "counts": counts, "n": n, "L": L, "ms_per_step": ms,
         "pairs": st["near_pairs"], "value": st["near_pairs"] / (ms * 1e-3), "stats": st,
-        "kernels": kernel_rooflines(prof, steps, mixed, bool(st["near_fft"]), p=q + 2, moments=moments,
+        "kernels": kernel_rooflines(prof, steps, mixed, st["near_path"], p=q + 2, moments=moments,
                                     default_screen=(sup == fp.SUPPORT_ONE and q == 3)),
         "stages_ms_per_step": {k: v["ms"] / steps for k, v in prof.items() if not k.startswith("fine_apply")},
         "out": {k: v.detach().cpu().numpy() for k, v in out.items()},
@@ -520,6 +528,39 @@ def variant_summary(r, ref=None):
             "U_rel": float(np.abs(r["out"]["U"] - ref["out"]["U"]).max() / np.abs(ref["out"]["U"]).max()),
         }
     return v
+
+
+HEADLINE = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling",
+            "vs_baseline", "dtype", "data", "config")
+
+
+def headline(out):
+    """The printed line of a full record: the headline whole, then the step's stages and one or two figures of each
+    kernel, variant and sweep row, under 4 kB."""
+    def g(v):
+        return float(f"{v:.4g}") if isinstance(v, float) else v
+
+    line = {k: out[k] for k in HEADLINE}
+    roof = out["roofline"]
+    line["roofline"] = {k: g(roof[k]) for k in ("kernel", "bound", "achieved", "peak", "unit", "frac", "traffic",
+                                                "avg_launch_ms") if not isinstance(roof.get(k), (dict, list))
+                        and k in roof}
+    line["kernels_ms_frac"] = {k.split(" (")[0]: [g(v["avg_launch_ms"]), g(v["frac"])] for k, v in out["kernels"].items()}
+    line["stages_ms"] = {k: g(v) for k, v in out["stages_ms_per_step"].items() if v}
+    for k in ("mg_iterations", "mg_rel_residual", "create_seconds", "practical_hbm_gbs"):
+        line[k] = g(out.get(k))
+    for k in ("method_error_vs_ewald", "method_error_vs_ewald_full_size"):
+        if out.get(k):
+            line[k] = {e: g(out[k][e]) for e in ("Phi_rel_rms", "F_rel_rms") if e in out[k]}
+    if out.get("cpu_baseline"):
+        line["cpu_baseline"] = {k: g(v) for k, v in out["cpu_baseline"].items() if isinstance(v, (int, float))}
+    if out.get("variants"):
+        line["variants_ms"] = {k: g(v["ms_per_step"]) for k, v in out["variants"].items()}
+    if out.get("screen_sweep"):
+        line["screens_ms_err"] = {f"{r['screen']} {r['near_block']}": [g(r["ms_per_step"]),
+                                                                       g(r["ewald"]["Phi_rel_rms"]) if r["ewald"] else None]
+                                  for r in out["screen_sweep"]["rows"]}
+    return line
 
 
 def main():
@@ -683,7 +724,10 @@ def main():
             out["cpu_baseline"] = cpu_baseline(r["workload"], args.cpu_sample, r["out"]["F"])
         else:
             out["cpu_baseline"] = None
-    print(json.dumps(out), flush=True)
+    if args.record:
+        with open(args.record, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(headline(out)), flush=True)
 
 
 if __name__ == "__main__":
