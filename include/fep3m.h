@@ -266,7 +266,8 @@ typedef struct {
  * forces are accumulated in the same pass); bytes that must cross HBM for
  * NEAR and ADJ_NEAR on the FFT path (what each of their launches reads and
  * writes: the table spectrum once per product, every FFT pass's array in and
- * out) and for FINE_APPLY (the vectors each launch reads and writes, 8 bytes
+ * out; on the lattice path the floating point operations of the transforms and
+ * products that ran) and for FINE_APPLY (the vectors each launch reads and writes, 8 bytes
  * per DOF each) and for MOMENTS (sorted positions and charges in, 32 bytes
  * per charge, the element starts and moments), LOAD (the moments in, the
  * load vector out), DEPOSIT (positions and charges in, the per-element

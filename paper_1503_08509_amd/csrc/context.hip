@@ -1428,7 +1428,10 @@ void fep3m_ctx::solve(const double *rhs, double *sol, int which) {
   // the iterate nor the direction, so a wrong guess costs its time alone.
   // That time passes the idle one's hundredfold on large meshes: up to 2^23
   // unknowns (32^3 elements with forces).  1000 charges on 8^3: 975 -> 846
-  // us, 60000 on 24^3 (27-element screen): 2.42 -> 2.30 ms.
+  // us, 60000 on 24^3 (27-element screen): 2.42 -> 2.30 ms.  On 32^3 4.59 -> 4.54
+  // ms; above, little is left to gain (without and with it 7.11 and 7.07 ms on
+  // 36^3, 12.78 and 12.75 on 45^3, 21.65 and 21.60 on 54^3, 32.27 and 32.23 on
+  // 64^3) while a wrong guess costs a V-cycle of 5 ms there.
   double relmax = 1.0, rate = 1e-2;
   int it = 0;
   const int step = mixed ? kPcgBetaPR : kPcgBeta;

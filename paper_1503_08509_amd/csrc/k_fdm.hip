@@ -71,9 +71,10 @@ __device__ __forceinline__ void dft(double2 (&v)[R]) {
 // W[f][k][i]: component k of mode i of frequency f; lam[f][i].
 //
 // Bound by float64 arithmetic (the six 1-D products, 9600 complex dots of p
-// per 64 x 125 values) and LDS, at one block of 16 waves per compute unit for
-// p = 5, n = 64 (128 KB); the next column's values are loaded into registers
-// meanwhile.  A wave takes whole slots, p^2 lines at a time, so the products'
+// per 64 x 125 values), LDS and, at one block of 16 waves per compute unit for
+// p = 5, n = 64 (128 KB), the latency of each column's loads, which nothing
+// overlaps: the next column's values held in registers meanwhile spilled (644 to
+// 810 us against 516 at 64^3, p = 5).  A wave takes whole slots, p^2 lines at a time, so the products'
 // steps need no block barrier, and W is uniform (x, y) or read by broadcast
 // (z).  Separate z passes and a solve of one block per frequency triple took
 // 235 + 551 + 223 us at 64^3, p = 5 (three trips through memory); this 516.

@@ -21,7 +21,7 @@
 // registers (with 36 the compiler moved them through vector lanes and the
 // marching form took 0.92 and 0.81 ms); the row strides keep 16 consecutive
 // lanes on distinct bank pairs (conflict cycles 6.6e7 to 2.1e7 per launch).
-// Now 0.62 and 0.47 ms, 84 vector instructions per node; on 32^3 elements
+// Now 0.62 and 0.47 ms, 104 vector instructions per node (average over the modes); on 32^3 elements
 // 0.085 to 0.058 ms, on 16^3 16.4 to 11.7 us, on 8^3 7.8 to 5.1 us.
 // Two blocks of 12 waves per compute unit overlap one block's memory phase
 // with the other's passes, which is why the registers are held to 80:

@@ -12,7 +12,9 @@
 // thread sums three values per plane (centre, sides, corners of the 3 x 3
 // square) and reuses them along its run of nodes in z.  (The iterate and right
 // side held in registers over a level's visit, a fifth fewer LDS reads: 31.4
-// against 30.6 us from 16^3.)  Above 20^3 two iterates no longer fit the LDS.
+// against 30.6 us from 16^3.)  21^3 would fit too (157 kB with its 7^3 level) but
+// has not been timed in this form and keeps its launches; from 22^3 two iterates
+// do not fit the LDS.
 #include <algorithm>
 
 #include "kernels.hpp"

@@ -15,7 +15,8 @@ struct MarchPlan {
 
 // The march length of least cost: rounds of resident blocks times the steps of
 // one (the start of a march costs 0.6 of a step: one element's planes and
-// carried rows), for sys systems.
+// carried rows), for sys systems.  resident: what the chip's 256 compute units
+// hold, two blocks of the large tiles or four of the small.
 inline MarchPlan plan_for(int n, int sys, int tx, int ty, int resident) {
   MarchPlan best{};
   double cost = 1e300;
@@ -42,6 +43,10 @@ constexpr bool tile_wraps(int n, int t) { return (n + t - 1) / t * t < 2 * n; }
 // against 6.9; on 16^3 13.1 against 11.7).  Order 3: 4 x 4 columns 14.2
 // against 14.7 us for 8 x 4 on 32^3, 135 against 104 us on 64^3 (a Chebyshev
 // step), where their rows of 12 nodes leave half of each cache line to others.
+// In between neither is better throughout (whole evaluations with forces, 4 x 4
+// and 8 x 4: 6.25 and 6.16 ms on 33^3, 8.75 and 8.94 on 40^3, 12.75 and 12.78 on
+// 45^3, 14.72 and 14.72 on 48^3, 21.17 and 21.64 on 54^3, 32.99 and 32.24 on 64^3,
+// by how the tiles divide the edge); the line is halfway.
 //
 // The length of the march suits the systems of the launch, except where sums
 // over a block follow from it (the dot products and the fused restriction,

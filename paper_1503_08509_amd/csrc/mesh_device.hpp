@@ -20,9 +20,9 @@ __device__ __forceinline__ double block_sum(double v, double *red) {
   return r;
 }
 
-// Fixed-shape block sum for any block of whole waves (up to 8): shuffle
-// tree inside each wave, then the wave sums in order.  The result is valid
-// in thread 0.
+// Fixed-shape block sum for any block of whole waves: shuffle tree inside
+// each wave, then the wave sums in order.  red holds a value per wave.  The
+// result is valid in thread 0.
 __device__ __forceinline__ double block_sum_waves(double v, double *red) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
