@@ -207,6 +207,8 @@ BATCH_WORKLOAD = "batch-64-n16"
 # sources are unchanged; otherwise traffic is reported as null.
 TRAFFIC_FILES = {
     "k_apply p=5 (fine-level operator)": ("k_apply_p5_fp64", ["paper_1503_08509_amd/csrc/k_march.hip",
+                                                               "paper_1503_08509_amd/csrc/march_plan.hpp",
+                                                               "paper_1503_08509_amd/csrc/index_wrap.hpp",
                                                                "paper_1503_08509_amd/csrc/mesh_device.hpp",
                                                                "paper_1503_08509_amd/csrc/device_common.hpp"]),
     "k_adj_moments (transposed near field)": ("k_adj_moments_fp64", ["paper_1503_08509_amd/csrc/k_adjoint.hip",

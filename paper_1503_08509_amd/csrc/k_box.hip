@@ -41,7 +41,8 @@ __device__ __forceinline__ int node_elem(int g, int PO, int n) { return min(g / 
 // over the 256 / nodes groups of threads.  Bound by the arithmetic of the
 // pairs and the LDS reads of their charges.  One thread per node left 2400
 // waves with a serial chain of loads each: 287 us at 32^3 elements with
-// 100000 charges (488 with eight lanes per node); 73 us so.
+// 100000 charges (488 with eight lanes per node); 90 us so (73 with roots of
+// one refining step, whose 4e-15 is 19 units in the last place).
 template <int PO>
 __global__ __launch_bounds__(256) void k_box_bvals(int n, int nsr, int nb, int64_t N, BoxNodes nodes,
                                                    const int *__restrict__ start, const double *__restrict__ sg,
@@ -338,7 +339,8 @@ __device__ __forceinline__ bool far_from_faces(const int (&Ec)[3], int n, int ns
 // the pairs: a lane steps its (row, column) without division, takes the
 // node coordinates from the wave's table and sums the face's two tangential
 // moments and the plain one (338 us at 32^3 elements with 100000 charges
-// when it worked each node out from its index; 134 us so).
+// when it worked each node out from its index; 159 us so, 134 with the short
+// roots).
 template <int PO>
 __global__ __launch_bounds__(256) void k_box_charge_bnd(int n, int nsr, int nb, int64_t N, const int *__restrict__ off,
                                                         double inv_h, BoxNodes nodes, const double *__restrict__ sg,
@@ -447,7 +449,7 @@ __global__ __launch_bounds__(256) void k_box_charge_bnd(int n, int nsr, int nb, 
 // The near block's charges are staged in LDS and split over two groups of
 // threads: bound by the arithmetic of the pairs.  Read one after the other
 // from memory by 100 threads they took 3.65 ms at 64^3 elements with 10^6
-// charges; 2.05 so.
+// charges; 2.25 so.
 template <int PO>
 __global__ __launch_bounds__(256) void k_box_flux(int n, int nsr, int64_t N, BoxQuad qd, const int *__restrict__ start,
                                                   const double *__restrict__ sg, const double *__restrict__ sQ,
@@ -619,7 +621,7 @@ __global__ __launch_bounds__(256) void k_box_h_slots(int n, int nb, const double
 // column) without division by a run-time value, takes the coordinates from
 // the wave's table and sums w / r^3, w / r^5 and the tangential moments of the
 // latter (5.21 ms at 64^3 elements with 10^6 charges when each point was
-// worked out from its index; 2.48 so).
+// worked out from its index; 2.69 so).
 template <int PO>
 __global__ __launch_bounds__(256) void k_box_flux_charge(int n, int nsr, int nb, int64_t N,
                                                          const int *__restrict__ off, double inv_h, BoxQuad qd,
