@@ -33,14 +33,10 @@ inline int conv_edge(int n, int nsr, bool box) {
   return N;
 }
 
-// Complex values of the spectrum (one octant, na moments, M nodes) and of the
-// work arrays of nb configurations.
+// Complex values of the spectrum (one octant, na moments, M nodes).
 inline size_t conv_spec_values(int N, int na, int M) {
   const size_t H = N / 2 + 1;
   return H * H * H * na * M;
-}
-inline size_t conv_work_values(int N, int na, int M, int nb) {
-  return size_t(N) * N * N * nb * 2 * ((na + 1) / 2 + (M + 1) / 2);
 }
 
 // Whether the transforms' arrays may take `bytes` of device memory, `spectrum`
